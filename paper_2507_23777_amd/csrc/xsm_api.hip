@@ -270,7 +270,7 @@ void forward_blocks_fast(xsm_ctx* c, int n_seq, int R, int len_bound, hipStream_
     q.X = X; q.ldx = d; q.gain = (const uint16_t*)P.g1; q.eps = g.rms_eps;
     q.Y = Qr; q.ldy = d; q.nscratch = Xn; q.ws_part = gpart; q.ws_tickets = gtick; q.pend = PEND;
     q.rope = rope; q.eff_len = eff; q.slot = slot; q.R = R; q.H = H; q.hd = hd; q.cap = c->cap_self;
-    q.v_transposed = 1; q.Kc = (uint16_t*)self_cache(c, l, 0); q.Vc = (uint16_t*)self_cache(c, l, 1);
+    q.Kc = (uint16_t*)self_cache(c, l, 0); q.Vc = (uint16_t*)self_cache(c, l, 1);
     fgemm(c, PRO_NORM, FEPI_QKV, q, s);
 
     FastAttn a{};
@@ -914,9 +914,7 @@ static int kv_debug(xsm_ctx* ctx, int32_t layer, int32_t which, int32_t slot, in
   char* base = cross ? cross_cache(ctx, layer, which - 2) : self_cache(ctx, layer, which);
   const int capp = cross ? ctx->cap_cross : ctx->cap_self;       // padded capacity
   char* rows = base + (size_t)slot * g.n_heads * capp * g.head_dim * ctx->esz;
-  const bool tr = ctx->fast && (which & 1);                       // values are cached transposed
-  const size_t st_h = (size_t)capp * g.head_dim;
-  const size_t st_p = tr ? 1 : (size_t)g.head_dim, st_i = tr ? (size_t)capp : 1;
+  const int layout = ctx->fast ? 1 + (which & 1) : 0;             // fragment order on the MFMA path
   // staged through the activation region of the workspace in pieces that fit
   const size_t stage_elems = (size_t)g.max_batch * kMaxRows * g.d_model * 2;   // X + Xn regions
   float* stage = (float*)(ctx->d_ws + ctx->ws.X);
@@ -931,11 +929,11 @@ static int kv_debug(xsm_ctx* ctx, int32_t layer, int32_t which, int32_t slot, in
         memcpy(&tmp[(size_t)h * np * g.head_dim], h_buf + ((size_t)h * n_pos + p) * g.head_dim,
                (size_t)np * g.head_dim * 4);
       XSM_HIP(hipMemcpy(stage, tmp.data(), n * 4, hipMemcpyHostToDevice));
-      launch_kv_convert(g.dtype, rows, stage, g.n_heads, pos0 + p, np, g.head_dim, st_h, st_p, st_i, 1, 0);
+      launch_kv_convert(g.dtype, rows, stage, g.n_heads, pos0 + p, np, g.head_dim, capp, layout, 1, 0);
       XSM_HIP(hipDeviceSynchronize());
     } else {
       XSM_HIP(hipDeviceSynchronize());
-      launch_kv_convert(g.dtype, rows, stage, g.n_heads, pos0 + p, np, g.head_dim, st_h, st_p, st_i, 0, 0);
+      launch_kv_convert(g.dtype, rows, stage, g.n_heads, pos0 + p, np, g.head_dim, capp, layout, 0, 0);
       XSM_HIP(hipMemcpy(tmp.data(), stage, n * 4, hipMemcpyDeviceToHost));
       for (int h = 0; h < g.n_heads; ++h)
         memcpy(h_buf + ((size_t)h * n_pos + p) * g.head_dim, &tmp[(size_t)h * np * g.head_dim],

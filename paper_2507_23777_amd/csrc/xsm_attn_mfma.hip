@@ -5,8 +5,8 @@
 // prefill passes with many tiles per sequence.
 //
 // HBM-bound: every cached key and value is read once per step, so the layout is chosen for
-// the loads.  Keys are [position][64] (128 B rows); values are stored transposed,
-// [64][capacity], so that both MFMA "A" operands are read with 16-byte lane loads:
+// the loads: 64-key chunks in the order of the MFMA "A" fragments (kfrag / vfrag), read with
+// contiguous 1 KB wavefront loads:
 //   S^T[key][query] = K[key][:] . Q[query][:]      A = 16 keys x 32 dims of K
 //   O^T[dim][query] = V^T[dim][key] . P^T[key][query]   A = 16 dims x 32 keys of V^T
 // A wavefront takes 64 keys at a time.  The 16-key score tiles are formed from keys
@@ -17,13 +17,10 @@
 // Online softmax in fp32 (base 2); the key range of one
 // (sequence, head) is split over S workgroups whose partial (max, sum, O) are merged in
 // fixed order by the last one to finish.
-#include "xsm_device.h"
+#include "xsm_attn_device.h"
 #include "xsm_internal.h"
 
 namespace xsm {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kPartFloats = (2 + 64) * 16;     // per split: m[16], l[16], O^T[64][16]
 
@@ -33,14 +30,6 @@ __device__ __forceinline__ void st_coherent(float* p, float v) {
 __device__ __forceinline__ float ld_coherent(const float* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ uint32_t pack2(float a, float b) { return f2bf_pair(a, b); }
-
-// (a, b) -> packed bf16 pair of the rounded values and of what the rounding dropped
-__device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t& lo) {
-  hi = pack2(a, b);
-  lo = pack2(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u));
-}
-
 // four consecutive dims (col % 4 == 0) of output row `row`: fp32, or operand planes for the projection that follows
 __device__ __forceinline__ void store_out4(const FastAttn& a, int row, int col, float4 v) {
   if (a.o_planes) plane_store4(a.O, a.o_rows, a.ldo, row, col, v);
@@ -48,105 +37,15 @@ __device__ __forceinline__ void store_out4(const FastAttn& a, int row, int col, 
 }
 
 // fp32 query row (64 dims at q, or nullptr for an MFMA column with no query) -> the lane's operand
-// halves (dims g*8.. and 32 + g*8..), each as bf16 hi and lo parts
+// halves
 __device__ __forceinline__ void load_queries(const FastAttn& a, bf16x8 (&qh)[2], bf16x8 (&ql)[2], const float* q, int g) {
+  float4 x[4];
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    float qv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (q) {
-      const float4 x0 = *reinterpret_cast<const float4*>(q + half * 32 + g * 8);
-      const float4 x1 = *reinterpret_cast<const float4*>(q + half * 32 + g * 8 + 4);
-      qv[0] = x0.x; qv[1] = x0.y; qv[2] = x0.z; qv[3] = x0.w;
-      qv[4] = x1.x; qv[5] = x1.y; qv[6] = x1.z; qv[7] = x1.w;
-    }
-    uint32_t hw[4], lw[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) split2(qv[2 * e], qv[2 * e + 1], hw[e], lw[e]);
-    qh[half] = __builtin_bit_cast(bf16x8, uint4{hw[0], hw[1], hw[2], hw[3]});
-    ql[half] = __builtin_bit_cast(bf16x8, uint4{lw[0], lw[1], lw[2], lw[3]});
+  for (int i = 0; i < 4; ++i) {
+    x[i] = float4{0.f, 0.f, 0.f, 0.f};
+    if (q) x[i] = *reinterpret_cast<const float4*>(q + (i >> 1) * 32 + g * 8 + (i & 1) * 4);
   }
-}
-
-// One 64-key chunk (keys key0..key0+63, fragments kf / vf as the cache loads deliver them) for the
-// wavefront's 16 queries: scores, online softmax (base 2), second product.  Query r sees keys
-// below lim; below first_masked every live query sees the key; keys at or past Ltot may hold
-// garbage (their values are zeroed so that 0 x garbage cannot become NaN).
-__device__ __forceinline__ void attn_chunk(const uint4 (&kf)[4][2], uint4 (&vf)[4][2], const bf16x8 (&qh)[2],
-                                           const bf16x8 (&ql)[2], int key0, int g, bool qlive, int lim,
-                                           int first_masked, int Ltot, float scale_log2, float& m_run,
-                                           float& l_run, f32x4 (&o)[4]) {
-  f32x4 sc[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    sc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const bf16x8 kk = __builtin_bit_cast(bf16x8, kf[t][half]);
-      sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk, ql[half], sc[t], 0, 0, 0);
-      sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk, qh[half], sc[t], 0, 0, 0);
-    }
-  }
-  // this lane's 16 scores belong to keys key0 + g*16 + t*4 + i
-  const int kbase = key0 + g * 16;
-  const bool edge = key0 + 64 > first_masked || !qlive;
-  float cmax = -INFINITY;
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float v = sc[t][i] * scale_log2;
-      if (edge && kbase + t * 4 + i >= lim) v = -INFINITY;
-      sc[t][i] = v;
-      cmax = fmaxf(cmax, v);
-    }
-  cmax = fmaxf(cmax, __shfl_xor(cmax, 16, WAVE));
-  cmax = fmaxf(cmax, __shfl_xor(cmax, 32, WAVE));
-  const float m_new = fmaxf(m_run, cmax);
-  const float m_use = m_new == -INFINITY ? 0.f : m_new;
-  const float alpha = exp2f(m_run - m_use);
-  float psum = 0.f;
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float p = exp2f(sc[t][i] - m_use);
-      sc[t][i] = p;
-      psum += p;
-    }
-  psum += __shfl_xor(psum, 16, WAVE);
-  psum += __shfl_xor(psum, 32, WAVE);
-  l_run = l_run * alpha + psum;
-  m_run = m_new;
-#pragma unroll
-  for (int dt = 0; dt < 4; ++dt) o[dt] *= alpha;
-  if (key0 + 64 > Ltot) {                         // slots past the live range hold garbage
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        uint32_t* w = reinterpret_cast<uint32_t*>(&vf[dt][jj]);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          if (kbase + jj * 8 + e >= Ltot) w[e >> 1] &= (e & 1) ? 0x0000FFFFu : 0xFFFF0000u;
-        }
-      }
-  }
-  uint4 ph[2], pl[2];
-#pragma unroll
-  for (int jj = 0; jj < 2; ++jj) {
-    split2(sc[2 * jj][0], sc[2 * jj][1], ph[jj].x, pl[jj].x);
-    split2(sc[2 * jj][2], sc[2 * jj][3], ph[jj].y, pl[jj].y);
-    split2(sc[2 * jj + 1][0], sc[2 * jj + 1][1], ph[jj].z, pl[jj].z);
-    split2(sc[2 * jj + 1][2], sc[2 * jj + 1][3], ph[jj].w, pl[jj].w);
-  }
-#pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-    for (int jj = 0; jj < 2; ++jj) {
-      const bf16x8 vv = __builtin_bit_cast(bf16x8, vf[dt][jj]);
-      o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv, __builtin_bit_cast(bf16x8, pl[jj]), o[dt], 0, 0, 0);
-      o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv, __builtin_bit_cast(bf16x8, ph[jj]), o[dt], 0, 0, 0);
-    }
+  split_queries(x, qh, ql);
 }
 
 __global__ __launch_bounds__(256) void k_fattn(const FastAttn a) {
@@ -189,17 +88,12 @@ __global__ __launch_bounds__(256) void k_fattn(const FastAttn a) {
     const int key0 = c << 6;
     uint4 kf[4][2], vf[4][2];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const uint16_t* kr = kb + (size_t)(key0 + (r >> 2) * 16 + t * 4 + (r & 3)) * 64 + g * 8;
-      kf[t][0] = *reinterpret_cast<const uint4*>(kr);
-      kf[t][1] = *reinterpret_cast<const uint4*>(kr + 32);
-    }
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt) {
-      const uint16_t* vr = vb + (size_t)(dt * 16 + r) * a.cap + key0 + g * 16;
-      vf[dt][0] = *reinterpret_cast<const uint4*>(vr);
-      vf[dt][1] = *reinterpret_cast<const uint4*>(vr + 8);
-    }
+      for (int j = 0; j < 2; ++j) {
+        kf[t][j] = *reinterpret_cast<const uint4*>(kb + (size_t)c * 4096 + (t * 2 + j) * 512 + lane * 8);
+        vf[t][j] = *reinterpret_cast<const uint4*>(vb + (size_t)c * 4096 + (t * 2 + j) * 512 + lane * 8);
+      }
     attn_chunk(kf, vf, qh, ql, key0, g, r < R, lim, first_masked, Ltot, a.scale_log2, m_run, l_run, o);
   }
 
@@ -289,14 +183,12 @@ __global__ __launch_bounds__(256) void k_pattn(const FastAttn a) {
   const uint16_t* vb = a.Vt + head * 64 * (size_t)a.cap;
   // wavefront w requests key tile w and value tile w of a chunk (the same addresses k_fattn loads)
   auto request = [&](int c) {
-    const int key0 = c << 6;
     unsigned char* dst = kv[c & 1];
-    const uint16_t* kr = kb + (size_t)(key0 + (r >> 2) * 16 + wave * 4 + (r & 3)) * 64 + g * 8;
-    lds_direct16(kr, dst + (wave * 2) * 1024);
-    lds_direct16(kr + 32, dst + (wave * 2 + 1) * 1024);
-    const uint16_t* vr = vb + (size_t)(wave * 16 + r) * a.cap + key0 + g * 16;
-    lds_direct16(vr, dst + 8192 + (wave * 2) * 1024);
-    lds_direct16(vr + 8, dst + 8192 + (wave * 2 + 1) * 1024);
+    const size_t o = (size_t)c * 4096 + wave * 1024 + lane * 8;
+    lds_direct16(kb + o, dst + (wave * 2) * 1024);
+    lds_direct16(kb + o + 512, dst + (wave * 2 + 1) * 1024);
+    lds_direct16(vb + o, dst + 8192 + (wave * 2) * 1024);
+    lds_direct16(vb + o + 512, dst + 8192 + (wave * 2 + 1) * 1024);
   };
   // a workgroup takes 64-row block x and then block NQ - 1 - x: under the causal mask the later a
   // block, the more keys it walks, and the two together walk the same number for every workgroup

@@ -115,9 +115,8 @@ __device__ __forceinline__ void qkv_store(const FastGemm& g, int nt, int nrow, i
   }
   const size_t head = (size_t)g.slot[b] * g.H + h;
   if (sec == 0) g.Y[(size_t)m * g.ldy + h * g.hd + dim] = o;
-  else if (sec == 1) g.Kc[(head * g.cap + pos) * g.hd + dim] = f2bf(o);
-  else if (g.v_transposed) g.Vc[(head * g.hd + dim) * g.cap + pos] = f2bf(o);
-  else g.Vc[(head * g.cap + pos) * g.hd + dim] = f2bf(o);
+  else if (sec == 1) g.Kc[head * g.cap * 64 + kfrag(pos, dim)] = f2bf(o);
+  else g.Vc[head * g.cap * 64 + vfrag(pos, dim)] = f2bf(o);
 }
 
 template <int PRO, int EPI, int MT>
@@ -493,12 +492,11 @@ __device__ __forceinline__ void qkv_pair_store(const FastGemm& g, const QkvCols&
   if (c.sec == 0) {
     *reinterpret_cast<float2*>(g.Y + (size_t)m * g.ldy + c.h * g.hd + c.dim0) = o;
   } else if (c.sec == 1) {
-    *reinterpret_cast<uint32_t*>(g.Kc + (head * g.cap + pos) * g.hd + c.dim0) = pack_bf16(o.x, o.y);
-  } else if (g.v_transposed) {
-    g.Vc[(head * g.hd + c.dim0) * g.cap + pos] = f2bf(o.x);
-    g.Vc[(head * g.hd + c.dim0 + 1) * g.cap + pos] = f2bf(o.y);
+    *reinterpret_cast<uint32_t*>(g.Kc + head * g.cap * 64 + kfrag(pos, c.dim0)) = pack_bf16(o.x, o.y);
   } else {
-    *reinterpret_cast<uint32_t*>(g.Vc + (head * g.cap + pos) * g.hd + c.dim0) = pack_bf16(o.x, o.y);
+    uint16_t* v = g.Vc + head * g.cap * 64 + vfrag(pos, c.dim0);
+    v[0] = f2bf(o.x);
+    v[8] = f2bf(o.y);
   }
 }
 
@@ -772,12 +770,11 @@ __device__ __forceinline__ void qkv_quad_store(const FastGemm& g, const QkvCols&
   if (c.sec == 0) {
     *reinterpret_cast<f32x4*>(g.Y + (size_t)q.m * g.ldy + c.h * g.hd + c.dim0) = o;
   } else if (c.sec == 1) {
-    *reinterpret_cast<uint2*>(g.Kc + (head * g.cap + q.pos) * g.hd + c.dim0) = uint2{pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3])};
-  } else if (g.v_transposed) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) g.Vc[(head * g.hd + c.dim0 + e) * g.cap + q.pos] = f2bf(o[e]);
+    *reinterpret_cast<uint2*>(g.Kc + head * g.cap * 64 + kfrag(q.pos, c.dim0)) = uint2{pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3])};
   } else {
-    *reinterpret_cast<uint2*>(g.Vc + (head * g.cap + q.pos) * g.hd + c.dim0) = uint2{pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3])};
+    uint16_t* v = g.Vc + head * g.cap * 64 + vfrag(q.pos, c.dim0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e * 8] = f2bf(o[e]);
   }
 }
 

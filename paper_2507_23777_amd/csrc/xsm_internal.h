@@ -61,7 +61,7 @@ void flush_pending_add(PendingAdd* p, hipStream_t s);
 struct LayerTab {
   const uint4 *Wqkv, *Wo, *W1, *W2;     // fragment-ordered weights
   const uint16_t *g1, *g2;              // RMSNorm gains (bf16)
-  uint16_t *Kc, *Vt;                    // this layer's key cache and transposed value cache
+  uint16_t *Kc, *Vt;                    // this layer's key and value cache (fragment order)
 };
 
 }  // namespace xsm
@@ -76,7 +76,7 @@ struct xsm_ctx {
   size_t weights_bytes, kv_bytes;
   size_t kv_self_elems;    // elements of the self-attention cache (cross cache follows)
   size_t kv_cross_elems;   // elements of the layers' cross cache (the heads' condition cache follows)
-  bool fast = false;       // bf16 MFMA path (head_dim 64, values cached transposed)
+  bool fast = false;       // bf16 MFMA path (head_dim 64, cache in fragment order)
   bool small_ok = false;   // single-launch step available for this model shape
   bool use_small = true;   // xsm_set_option(XSM_OPT_SINGLE_LAUNCH)
   bool small_dev = false;  // the bound device can hold the single launch's 256 workgroups at once
@@ -162,7 +162,7 @@ void launch_rope_kv(int dtype, const float* QKV, const float2* rope, const int32
                     int hd, int max_ctx, hipStream_t s);
 // cond K/V rows of one chunk into the cross cache: KV[M][2d] -> caches at rows row0..row0+C-1
 void launch_store_cond(int dtype, const float* KV, const int32_t* slot, void* Kc, void* Vc,
-                       int n_seq, int C, int row0, int H, int hd, int cap, int v_transposed,
+                       int n_seq, int C, int row0, int H, int hd, int cap, int frag_order,
                        hipStream_t s);
 // attention of row m = b*R + j over cache positions < (fixed_limit > 0 ? fixed_limit
 // : eff_len[b] + j + 1)
@@ -190,7 +190,7 @@ struct FastGemm {
   PendingAdd* pend;            // host-side: where a residual-add projection may leave its sum pending
   // FEPI_QKV
   const float2* rope; const int32_t* eff_len; const int32_t* slot;
-  int R, H, hd, cap, v_transposed;
+  int R, H, hd, cap;
   uint16_t* Kc; uint16_t* Vc;
 };
 bool fgemm_supported(int N, int K);
@@ -211,8 +211,8 @@ void launch_copy_u16(const void* src, void* dst, int n, hipStream_t s);
 
 struct FastAttn {
   const float* Q; int ldq;            // fp32 rotated queries [M][d]
-  const uint16_t* Kc;                 // layer's keys [slot][H][cap][64]
-  const uint16_t* Vt;                 // layer's values, transposed [slot][H][64][cap]
+  const uint16_t* Kc;                 // layer's keys and values [slot][H][cap * 64], fragment order
+  const uint16_t* Vt;
   const int32_t* eff_len; const int32_t* slot;
   float* O; int ldo;                  // fp32 output [M][d]
   int o_planes, o_rows;               // o_planes: write O as operand planes [o_rows][ldo] instead (o_rows = M)
@@ -274,10 +274,9 @@ void launch_emit(const float* Zh, const xsm_verify_params& vp, const int32_t* ef
                  int32_t* out_tokens, int32_t* n_accepted, uint32_t* flags, int n_seq, int R, int K, int V,
                  hipStream_t s);
 void launch_copy_f32(const float* src, float* dst, size_t n, hipStream_t s);
-// cache <-> float staging [H][n_pos][hd]; element (h, p, i) of the slot lives at
-// base[h*stride_h + p*stride_p + i*stride_i]
+// cache of one slot <-> float staging [H][n_pos][hd]; layout: 0 rows [pos][hd], 1 keys / 2 values in
+// fragment order
 void launch_kv_convert(int dtype, void* slot_base, float* staging, int H, int pos0, int n_pos,
-                       int hd, size_t stride_h, size_t stride_p, size_t stride_i, int to_cache,
-                       hipStream_t s);
+                       int hd, int cap, int layout, int to_cache, hipStream_t s);
 
 }  // namespace xsm

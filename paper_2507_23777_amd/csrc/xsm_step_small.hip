@@ -801,21 +801,15 @@ __global__ __launch_bounds__(256) void k_step_small(const SmallArgs a) {
     auto first_chunk = [&]() {
       const bool use = c_lo + wave < c_hi;
       const int m = opaque_mask(use);
-      const int key0 = (c_lo + wave) << 6;
-      const gptr16 kq = as_global(kb), vq = as_global(vb);             // 16-byte pieces
+      const gptr16 kq = as_global(kb), vq = as_global(vb);             // 16-byte pieces, 512 per chunk
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int piece = ((key0 + (r >> 2) * 16 + t * 4 + (r & 3)) * 8 + g) & m;    // 8 pieces per key row
-        kf[t][0] = ldg16(kq, piece);
-        kf[t][1] = ldg16(kq, piece + (4 & m));
-      }
-      const int capp = a.cap >> 3;                                      // pieces per value row
+      for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt) {
-        const int piece = ((dt * 16 + r) * capp + (key0 >> 3) + g * 2) & m;
-        vf[dt][0] = ldg16(vq, piece);
-        vf[dt][1] = ldg16(vq, piece + (1 & m));
-      }
+        for (int j = 0; j < 2; ++j) {
+          const int piece = ((c_lo + wave) * 512 + (t * 2 + j) * 64 + lane) & m;
+          kf[t][j] = ldg16(kq, piece);
+          vf[t][j] = ldg16(vq, piece);
+        }
     };
 
     // OPROJ workgroups: their element of the residual entering the layer (four partial words),
@@ -869,10 +863,10 @@ __global__ __launch_bounds__(256) void k_step_small(const SmallArgs a) {
           const uint16_t ob = f2bf(o);
           if (q_sec == 1) {
             st32(lb + OFF_KN + col, bf2f(ob), t8);
-            lt.Kc[(head * a.cap + pos) * 64 + dim] = ob;
+            lt.Kc[head * a.cap * 64 + kfrag(pos, dim)] = ob;
           } else {
             st32(lb + OFF_VN + col, bf2f(ob), t8);
-            lt.Vt[(head * 64 + dim) * a.cap + pos] = ob;
+            lt.Vt[head * a.cap * 64 + vfrag(pos, dim)] = ob;
           }
         }
       }
@@ -891,18 +885,11 @@ __global__ __launch_bounds__(256) void k_step_small(const SmallArgs a) {
       // bytes of a request land at base + 16 l, i.e. already in fragment order), 16 KB per wavefront
       unsigned char* const ring = dyn + 16384 + wave * 16384;
       auto request_next = [&](int c) {
-        const int key0 = c << 6;
+        const size_t o = (size_t)c * 4096 + lane * 8;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const uint16_t* kr = kb + (size_t)(key0 + (r >> 2) * 16 + t * 4 + (r & 3)) * 64 + g * 8;
-          lds_direct16(kr, ring + (t * 2) * 1024);
-          lds_direct16(kr + 32, ring + (t * 2 + 1) * 1024);
-        }
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt) {
-          const uint16_t* vr = vb + (size_t)(dt * 16 + r) * a.cap + key0 + g * 16;
-          lds_direct16(vr, ring + 8192 + (dt * 2) * 1024);
-          lds_direct16(vr + 8, ring + 8192 + (dt * 2 + 1) * 1024);
+        for (int f = 0; f < 8; ++f) {
+          lds_direct16(kb + o + f * 512, ring + f * 1024);
+          lds_direct16(vb + o + f * 512, ring + 8192 + f * 1024);
         }
       };
       auto take_next = [&]() {                              // (waits for the requests above)
