@@ -105,6 +105,12 @@ void build_work_offsets(const xsm_ctx* c, bool step_only, WorkOff& w, size_t& ro
     w.gpart = take(fl * 4);
     w.gtickets = take(kWsTickets * 4);
   }
+  w.lctrl = w.lssq = w.lerr = 0;
+  if (c->layers_ok) {
+    w.lctrl = take(layers_ctrl_bytes());
+    w.lssq = take((size_t)2 * kLayersMaxRows * (d / 16) * 4);
+    w.lerr = take(256);
+  }
   w.ll = w.ctrl = w.head_all = w.tlog = 0;
   if (c->small_ok && !step_only) {
     w.ll = take(small_ll_words(g.n_layers, g.d_model, g.d_ffn, g.n_draft) * 4);
@@ -355,6 +361,40 @@ void forward_blocks(xsm_ctx* c, int n_seq, int R, int len_bound, hipStream_t s) 
   }
 }
 
+// One pass of all layers as the persistent kernel; b names the rows (tokens or prefix embeddings).
+// kv_only: a prefill pass, whose result is the cache alone.
+void run_layers(xsm_ctx* c, LayersBegin b, bool kv_only, uint32_t* wflags, hipStream_t s) {
+  const xsm_config& g = c->cfg;
+  char* ws = c->d_ws;
+  const size_t d = g.d_model, Mp = ((size_t)b.n_seq * b.R + 15) & ~(size_t)15, blk = Mp * d * 4;
+  LayersArgs a{};
+  a.wts = (const LayerWts*)(c->d_w + c->layer_wts_off); a.L = g.n_layers; a.kv_only = kv_only ? 1 : 0;
+  a.x[0] = (float*)(ws + c->ws.QKV); a.x[1] = (float*)(ws + c->ws.QKV + blk);
+  a.P[0] = ws + c->ws.QKV + 2 * blk; a.P[1] = ws + c->ws.Xn;
+  a.ssq[0] = (float*)(ws + c->ws.lssq); a.ssq[1] = a.ssq[0] + Mp * (d / 16);
+  a.q = (float*)(ws + c->ws.Qr); a.AO = ws + c->ws.AO; a.U = ws + c->ws.U;
+  a.part = (float*)(ws + c->ws.part); a.tickets = (uint32_t*)(ws + c->ws.tickets);
+  a.gpart = (float*)(ws + c->ws.gpart); a.gtickets = (uint32_t*)(ws + c->ws.gtickets);
+  a.x_out = (float*)(ws + c->ws.X);
+  a.eff_len_w = (int32_t*)(ws + c->ws.eff_len); a.eff_len = a.eff_len_w; a.slot = (const int32_t*)(ws + c->ws.slot);
+  a.wflags = wflags; a.err = (uint32_t*)(ws + c->ws.lerr);
+  a.rope = (const float2*)(c->d_w + c->rope_off); a.ctrl = (uint32_t*)(ws + c->ws.lctrl);
+  a.eps = g.rms_eps; a.scale_log2 = 1.4426950408889634f / sqrtf((float)g.head_dim);
+  a.cap = c->cap_self; a.cap_cross = c->cap_cross; a.n_cond = g.n_cond;
+  b.gain = (const uint16_t*)layer_ptrs(c, 0).g1;
+  b.eff_len = a.eff_len_w; b.slot_out = (int32_t*)(ws + c->ws.slot); b.wflags = wflags;
+  launch_layers(b, a, g.d_model, s);
+}
+
+// attention's arrival counters in the bound workspace start at zero (and return to zero in every pass)
+void clear_tickets(xsm_ctx* ctx, hipStream_t s) {
+  const xsm_config& g = ctx->cfg;
+  size_t attn_pairs = (size_t)g.max_batch * g.n_heads * (g.head_kind == XSM_HEAD_CA && g.n_draft ? g.n_draft : 1);
+  if (attn_pairs < ctx->rows_max / 16 * g.n_heads) attn_pairs = ctx->rows_max / 16 * g.n_heads;
+  launch_fill_i32((int32_t*)(ctx->d_ws + ctx->ws.tickets), (int)attn_pairs, 0, s);
+  if (ctx->fast) launch_fill_i32((int32_t*)(ctx->d_ws + ctx->ws.gtickets), (int)kWsTickets, 0, s);
+}
+
 int check_ready(xsm_ctx* ctx) {
   if (!ctx) return XSM_EINVAL;
   if (!ctx->d_w || !ctx->d_kv || !ctx->d_ws) return fail(ctx, XSM_ESTATE, "buffers not bound");
@@ -450,10 +490,17 @@ int step_common(xsm_ctx* ctx, const xsm_batch* bt, const xsm_verify_params* vp, 
     if (e3 != hipSuccess) return fail(ctx, XSM_EHIP, std::string("launch: ") + hipGetErrorString(e3));
     return XSM_OK;
   }
-  launch_prepare(bt->kv_len, bt->slot, bt->block, n_seq, R, V, g.max_batch, g.max_ctx,
-                 bt->kv_len_bound, eff, slot, wfl, s);
-  launch_embed(dt, wb + ctx->woff.E * e, bt->block, eff, X, n_seq, R, d, s);
-  forward_blocks(ctx, n_seq, R, bt->kv_len_bound, s);
+  if (ctx->layers_ok && !ctx->layers_failed && layers_usable(n_seq, R)) {
+    LayersBegin b{};
+    b.E = (const uint16_t*)(wb + ctx->woff.E * e); b.block = bt->block; b.kv_len = bt->kv_len; b.slot = bt->slot;
+    b.n_seq = n_seq; b.R = R; b.vocab = V; b.max_batch = g.max_batch; b.max_ctx = g.max_ctx; b.bound = bt->kv_len_bound;
+    run_layers(ctx, b, false, wfl, s);
+  } else {
+    launch_prepare(bt->kv_len, bt->slot, bt->block, n_seq, R, V, g.max_batch, g.max_ctx,
+                   bt->kv_len_bound, eff, slot, wfl, s);
+    launch_embed(dt, wb + ctx->woff.E * e, bt->block, eff, X, n_seq, R, d, s);
+    forward_blocks(ctx, n_seq, R, bt->kv_len_bound, s);
+  }
   if (ctx->fast) {
     // Eq. 3 logits straight from the residual stream: final RMSNorm is the GEMM prologue
     FastGemm z{};
@@ -587,6 +634,7 @@ int xsm_create(const xsm_config* cfg, xsm_ctx** out) {
             g.vocab % 16 == 0;
   c->small_ok = c->fast && g.n_cond == 0 && small_supported(g.d_model, g.d_ffn) && g.vocab <= 65536 &&
                 g.n_layers <= 48;
+  c->layers_ok = c->fast && layers_supported(g.d_model, g.d_ffn, g.n_layers);
   build_weight_offsets(c);
   {
     size_t n_tickets = 0;
@@ -616,6 +664,10 @@ int xsm_create(const xsm_config* cfg, xsm_ctx** out) {
   if (c->small_ok) {
     c->layer_tab_off = c->weights_bytes;
     c->weights_bytes += align_up(sizeof(LayerTab) * g.n_layers);
+  }
+  if (c->layers_ok) {
+    c->layer_wts_off = c->weights_bytes;
+    c->weights_bytes += align_up(sizeof(LayerWts) * g.n_layers);
   }
   c->kv_self_elems = (size_t)g.n_layers * 2 * g.max_batch * g.n_heads * c->cap_self * g.head_dim;
   c->kv_cross_elems = (size_t)g.n_layers * 2 * g.max_batch * g.n_heads * c->cap_cross * g.head_dim;
@@ -697,12 +749,25 @@ int xsm_load_weights(xsm_ctx* ctx, const void* h_canonical, size_t n_elems, xsm_
         launch_copy_u16(wb + ctx->woff.hb[k] * 2, wb + ctx->toff.hb + (size_t)k * d * 2, d, s);
       }
     }
-    {
-      size_t attn_pairs = (size_t)g.max_batch * g.n_heads * (g.head_kind == XSM_HEAD_CA && g.n_draft ? g.n_draft : 1);
-      if (attn_pairs < ctx->rows_max / 16 * g.n_heads) attn_pairs = ctx->rows_max / 16 * g.n_heads;
-      launch_fill_i32((int32_t*)(ctx->d_ws + ctx->ws.tickets), (int)attn_pairs, 0, s);
+    clear_tickets(ctx, s);
+    if (ctx->layers_ok) {
+      ctx->layer_wts.resize(g.n_layers);
+      for (int l = 0; l < g.n_layers; ++l) {
+        const LayerPtrs P = layer_ptrs(ctx, l);
+        const TiledLayer& T = ctx->toff.layer[l];
+        const bool x = g.n_cond > 0;
+        auto w = [&](size_t off) { return (const uint4*)(wb + off); };
+        ctx->layer_wts[l] = LayerWts{w(T.Wqkv), w(T.Wo), x ? w(T.Wcq) : nullptr, x ? w(T.Wco) : nullptr, w(T.W1), w(T.W2),
+                                     (const uint16_t*)P.gc, (const uint16_t*)P.g2,
+                                     (const uint16_t*)(l + 1 < g.n_layers ? layer_ptrs(ctx, l + 1).g1 : wb + ctx->woff.gf * 2),
+                                     (uint16_t*)self_cache(ctx, l, 0), (uint16_t*)self_cache(ctx, l, 1),
+                                     x ? (const uint16_t*)cross_cache(ctx, l, 0) : nullptr,
+                                     x ? (const uint16_t*)cross_cache(ctx, l, 1) : nullptr};
+      }
+      XSM_HIP(hipMemcpyAsync(wb + ctx->layer_wts_off, ctx->layer_wts.data(), sizeof(LayerWts) * g.n_layers,
+                             hipMemcpyHostToDevice, s));
+      launch_fill_i32((int32_t*)(ctx->d_ws + ctx->ws.lerr), 1, 0, s);
     }
-    launch_fill_i32((int32_t*)(ctx->d_ws + ctx->ws.gtickets), (int)kWsTickets, 0, s);
     if (ctx->small_ok) {
       ctx->layer_tab.resize(g.n_layers);
       for (int l = 0; l < g.n_layers; ++l) {
@@ -724,7 +789,7 @@ int xsm_load_weights(xsm_ctx* ctx, const void* h_canonical, size_t n_elems, xsm_
   }
   XSM_HIP(hipGetLastError());
   ctx->loaded = true;
-  ctx->small_failed = false;
+  ctx->small_failed = ctx->layers_failed = false;
   return XSM_OK;
 }
 
@@ -799,6 +864,13 @@ int xsm_prefill(xsm_ctx* ctx, int32_t n_seq, const int32_t* h_slot, const void* 
   }
   for (int r0 = 0; r0 < P; r0 += chunk) {
     const int C = P - r0 < chunk ? P - r0 : chunk;
+    if (ctx->layers_ok && !ctx->layers_failed && layers_usable(n_seq, C)) {
+      LayersBegin b{};
+      b.rows = (const uint16_t*)d_prefix_emb; b.rows_per_seq = P; b.row0 = r0;
+      b.n_seq = n_seq; b.R = C;
+      run_layers(ctx, b, true, nullptr, s);
+      continue;
+    }
     launch_fill_i32(eff, n_seq, r0, s);
     launch_load_rows(dt, d_prefix_emb, X, n_seq, C, r0, P, d, s);
     forward_blocks(ctx, n_seq, C, r0, s);
@@ -877,7 +949,23 @@ int xsm_debug_timeline(xsm_ctx* ctx, uint64_t* h_out, size_t n_words) {
 int xsm_check_device(xsm_ctx* ctx) {
   if (!ctx) return XSM_EINVAL;
   XSM_HIP(hipDeviceSynchronize());
-  if (!ctx->small_ok || !ctx->d_ws || !ctx->loaded) return XSM_OK;
+  if (!ctx->d_ws || !ctx->loaded) return XSM_OK;
+  if (ctx->layers_ok) {
+    uint32_t code = 0;
+    XSM_HIP(hipMemcpy(&code, ctx->d_ws + ctx->ws.lerr, 4, hipMemcpyDeviceToHost));
+    if (code != 0) {
+      // (attention's arrival counters may be half way: they start at zero again)
+      const uint32_t zero = 0;
+      XSM_HIP(hipMemcpy(ctx->d_ws + ctx->ws.lerr, &zero, 4, hipMemcpyHostToDevice));
+      clear_tickets(ctx, nullptr);
+      XSM_HIP(hipDeviceSynchronize());
+      ctx->layers_failed = true;
+      return fail(ctx, XSM_EDEVICE, "layers kernel: a wait for a stage timed out (code " + std::to_string(code) +
+                                        "); the sequences of that step carry n_accepted = 0 and XSM_FLAG_DEVICE_TIMEOUT, "
+                                        "later passes run on the per-stage kernels");
+    }
+  }
+  if (!ctx->small_ok) return XSM_OK;
   uint32_t c[2] = {0, 0};
   XSM_HIP(hipMemcpy(c, ctx->d_ws + ctx->ws.ctrl, 8, hipMemcpyDeviceToHost));
   if (c[1] != 0) {

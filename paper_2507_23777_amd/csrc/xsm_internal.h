@@ -34,6 +34,7 @@ struct WorkOff {
   size_t eff_len, slot, acc, y0, wflags, toks, rowidx, eff2, slot2;   // int32 arrays
   size_t part, tickets, gpart, gtickets;                                  // split-key attention partials
   size_t ll, ctrl, head_all, tlog;                       // single-launch step: exchange buffers
+  size_t lctrl, lssq, lerr;                              // persistent layers kernel: queues and partition, square sums, error word
   size_t total;
 };
 
@@ -46,7 +47,6 @@ struct TiledOff {
   bool wu_ok;              // vocabulary is a multiple of 16
 };
 
-// Per-layer pointers of the single-launch step (uploaded to the device at load time).
 // Output of a residual-add projection that is still in split-contraction partial blocks
 // [N/64][kspl][M][64]; the next RMSNorm pass over Y (or flush_pending_add) adds it in.
 struct PendingAdd {
@@ -58,6 +58,14 @@ struct PendingAdd {
 };
 void flush_pending_add(PendingAdd* p, hipStream_t s);
 
+// Per-layer pointers of the persistent layers kernel and of the single-launch step (uploaded to the
+// device at load time).
+struct LayerWts {
+  const uint4 *Wqkv, *Wo, *Wcq, *Wco, *W1, *W2;       // fragment-ordered weights
+  const uint16_t *gc, *g2, *g_next;                   // gains; g_next: the following layer's first norm (the last layer's: the final norm)
+  uint16_t *Kc, *Vt;                                  // key and value cache (fragment order)
+  const uint16_t *Kx, *Vx;                            // cross-attention keys / values
+};
 struct LayerTab {
   const uint4 *Wqkv, *Wo, *W1, *W2;     // fragment-ordered weights
   const uint16_t *g1, *g2;              // RMSNorm gains (bf16)
@@ -82,6 +90,10 @@ struct xsm_ctx {
   bool small_dev = false;  // the bound device can hold the single launch's 256 workgroups at once
   bool small_failed = false;   // xsm_check_device found a timed-out wait: per-stage kernels until weights are loaded again
   bool gemm_unmatched = false; // a projection found no kernel for its (prologue, epilogue) pair: the step reports it
+  bool layers_failed = false;  // xsm_check_device found a timed-out wait of it: per-stage kernels until weights are loaded again
+  bool layers_ok = false;  // persistent layers kernel available for this model shape
+  size_t layer_wts_off = 0;              // byte offset of the LayerWts array in the weights buffer
+  std::vector<xsm::LayerWts> layer_wts;  // host copy (source of the upload)
   bool timeline = false;   // xsm_set_option(XSM_OPT_TIMELINE)
   int force_splits = 0;    // xsm_set_option(XSM_OPT_ATTN_SPLITS): key-range slices per (sequence, head), 0 = automatic
   int prefill_rows = 0;              // XSM_OPT_PREFILL_ROWS: rows per prefill pass, 0 = what the workspace holds
@@ -229,6 +241,39 @@ void launch_head_ca_prep(const float* G, float* Rk, const int32_t* eff, const in
 // out[m][:] = RMSNorm(X[row_index ? row_index[m] : m][:]) * gain (fp32 in and out, bf16 gain)
 void launch_norm_rows(const float* X, int ldx, const int32_t* row_index, const uint16_t* gain, float eps, float* out,
                       int M, int K, hipStream_t s);
+
+// ---- all layers of a pass in one persistent kernel (xsm_layers.hip) ------------------
+constexpr int kLayersMaxRows = 1280;    // rows of a pass it takes (17 ..)
+enum { kStQkv = 0, kStAtt, kStO, kStCq, kStCatt, kStCo, kStUp, kStDown };
+constexpr int kMaxLayerStages = 8;
+struct LayerStage { int kind, NT, MT, KS, NG, MG, MC, base, count, adds_before; };   // base: first task number inside a layer
+struct LayersBegin {
+  const uint16_t* E; const int32_t* block; const int32_t* kv_len; const int32_t* slot;   // decoding: tokens and sequences
+  const uint16_t* rows; int rows_per_seq, row0;                                          // prefill: bf16 rows [n_seq][rows_per_seq][d]
+  const uint16_t* gain;                 // first norm
+  int n_seq, R, d, H, vocab, max_batch, max_ctx, bound;
+  int32_t* eff_len; int32_t* slot_out; uint32_t* wflags;
+  float* x; void* planes; float* ssq; uint32_t* ctrl; int32_t* unit_pre;                 // (set by launch_layers)
+};
+struct LayersArgs {
+  const LayerWts* wts; int L;
+  int kv_only;                          // the cache is all that is wanted: the last layer ends with its QKV stage
+  float* x[2]; void* P[2]; float* ssq[2];   // residual tiles, operand planes, square sums: each stage that adds writes the other one
+  float* q; void* AO; void* U; float* part; uint32_t* tickets; float* gpart; uint32_t* gtickets;
+  float* x_out;                         // final residual rows [M][d]
+  const int32_t* eff_len; int32_t* eff_len_w; const int32_t* slot; uint32_t* wflags; uint32_t* err;
+  const float2* rope; uint32_t* ctrl; const int32_t* unit_pre;
+  float eps, scale_log2;
+  int cap, cap_cross, n_cond;
+  // set by launch_layers
+  int M, mtiles, n_seq, R, n_stages, per_layer, adds;
+  LayerStage stage[kMaxLayerStages];
+};
+bool layers_supported(int D, int F, int L);
+bool layers_usable(int n_seq, int R);
+size_t layers_ctrl_bytes();
+size_t layers_part_bytes();
+void launch_layers(LayersBegin b, LayersArgs a, int D, hipStream_t s);
 
 // ---- single-launch step for <= 16 block rows (xsm_step_small.hip) -------------------
 struct SmallArgs {
