@@ -39,6 +39,7 @@
 // (another stream's kernel may hold compute units), so the grid drains without needing to be
 // co-resident.  Waits are bounded all the same: a workgroup that gives up marks every sequence
 // as skipped (XSM_FLAG_DEVICE_TIMEOUT) and raises the error word of xsm_check_device.
+#include <type_traits>
 #include "xsm_attn_device.h"
 #include "xsm_internal.h"
 
@@ -211,7 +212,7 @@ __global__ __launch_bounds__(256) void k_layers_begin(const LayersBegin a) {
 // ---------------------------------------------------------------------------
 struct Smem {
   union {
-    float4 red[kWaves * 8 * 64];                     // partial tiles of a projection
+    float4 red[2 * kWaves * 8 * 64];                  // partial tiles of a projection, two groups
     float slots[kWaves * 2 * kSlotFloats];            // attention results: two per wavefront
   };
   float inv[64];                                      // 1 / rms of the task's rows
@@ -240,12 +241,13 @@ __device__ __forceinline__ TaskPos task_pos(const LayersArgs& a, int t, int from
 // Position of a projection task: the slices of one weight group, then its row chunks follow each other
 // on one XCD (task numbers go round the queues, queues round the XCDs), so an XCD's L2 sees a
 // weight once.  Row groups mg0 .. mg1 - 1.
-struct Tile { int ng, ks, mg0, mg1; };
+struct Tile { int ng, ks, mc, mg0, mg1; };
 __device__ __forceinline__ bool tile_pos(const LayerStage& st, int idx, Tile* t) {
   if (idx >= st.NG * st.MC * st.KS) return false;     // (numbers that only fill a stage up to whole queues)
   const int x = idx & 7, i = idx >> 3, j = st.KS == 1 ? i : i >> 2, q = j / st.MC, mc = j - q * st.MC;
   t->ks = st.KS == 1 ? 0 : i & 3;
   t->ng = q * 8 + x;
+  t->mc = mc;
   t->mg0 = mc * st.MG / st.MC;
   t->mg1 = (mc + 1) * st.MG / st.MC;
   return true;
@@ -340,6 +342,31 @@ __device__ __forceinline__ void qkv_out(const LayersArgs& a, const LayerWts* w, 
   }
 }
 
+// A residual-add projection's four columns n0.. of row m: the new residual u, its operand planes for the
+// next norm (gain g) and its square sum; or, at the end of the pass, the fp32 row.
+template <int D>
+__device__ __forceinline__ void add_out(const LayersArgs& a, int cur, bool last, int m, int n0, unsigned xoff, int lane, f32x4 u,
+                                        float4 g) {
+  constexpr int NP = D / 16;
+  const int Mp = a.mtiles * 16;
+  if (last) {
+    if (m < a.M) *reinterpret_cast<f32x4*>(a.x_out + (size_t)m * D + n0) = u;
+    return;
+  }
+  const rsrc_t ro = make_rsrc(a.x[cur ^ 1], (size_t)Mp * D * 4), rp = make_rsrc(a.P[cur ^ 1], (size_t)Mp * D * 4);
+  stc16(ro, xoff, u);
+  planes4<D>(rp, (unsigned)Mp * D * 2u, m, n0, float4{u[0] * g.x, u[1] * g.y, u[2] * g.z, u[3] * g.w});
+  float s = u[0] * u[0] + u[1] * u[1] + u[2] * u[2] + u[3] * u[3];
+  s += lane_xor<16>(s); s += lane_xor<32>(s);
+  if (lane < 16) st_coh(a.ssq[cur ^ 1] + (size_t)m * NP + (n0 >> 4), s);
+}
+
+// largest ring of at most `most` k-tiles that divides a group's KW, so that a slot means the same k-tiles in every group
+constexpr int ring_depth(int KW, int most) {
+  int d = most < KW ? most : KW;
+  while (KW % d) --d;
+  return d;
+}
 // One projection task: its weights stay in registers while it goes through its row groups; while a
 // group's partial tiles are summed and stored, the next group's first activations are on their
 // way.  cur: which of the two residual / plane / square-sum buffers holds the rows.  SPLIT: the contraction in four slices
@@ -347,9 +374,10 @@ __device__ __forceinline__ void qkv_out(const LayersArgs& a, const LayerWts* w, 
 template <int D, int NT, int MT, int KW, bool SPLIT, typename Wait, typename Claim>
 __device__ __forceinline__ bool gemm_task(Smem& sm, const Wait& wait, const Claim& claim, int layer, int st_no, const LayerWts* w,
                                           int cur, bool last, Tile tl) {
+  static_assert(NT * MT <= kWaves && MT <= 2, "a wavefront finishes at most one tile; sixteen threads per row");
   constexpr int NP = D / 16;                          // square sums per row
-  constexpr int DEPTH = (8 / MT) < KW ? 8 / MT : KW;  // k-tiles of activations in flight
-  constexpr int NIT = (NT * MT + kWaves - 1) / kWaves;
+  constexpr bool WHOLE = KW > D / 256;                // FFN-down in one piece: one row group per task
+  constexpr int DEPTH = ring_depth(KW, (NT * KW > 16 && !WHOLE ? 4 : 8) / MT);   // k-tiles of activations in flight
   const LayersArgs& a = fresh_args();
   const LayerStage& st = a.stage[st_no];
   const int tid = fresh(threadIdx.x), wave = uni(tid >> 6), lane = tid & 63, kind = st.kind;
@@ -360,75 +388,71 @@ __device__ __forceinline__ bool gemm_task(Smem& sm, const Wait& wait, const Clai
   const uint4* const W = stage_weights(kind, w);
   const void* in = kind == kStDown ? a.U : (kind == kStO || kind == kStCo) ? a.AO : a.P[cur];
   const unsigned in_lo = (unsigned)Mp * KT * 64u;     // bytes of one plane
-  const rsrc_t rin = make_rsrc(in, (size_t)in_lo * 2);
-  f32x4* const red = reinterpret_cast<f32x4*>(sm.red);
-  // What the finishing threads will need: wavefront w finishes tiles w, w + 8 (n-tile t, row tile q).
-  // None of it comes from the stage in front, so it is requested before the wait too.  (What is
+  const rsrc_t rin = make_rsrc(in, (size_t)in_lo * 2), rx = make_rsrc(a.x[cur], (size_t)Mp * D * 4);
+  // What the finishing threads will need: wavefront w finishes tile w of a group (n-tile t, row tile
+  // q).  None of it comes from the stage in front, so it is requested before the wait too.  (What is
   // loaded stays as it is until it is used: arithmetic here would wait for the load here.)
-  uint4 xin[NIT];
-  u32x2 gn[NIT];
-  QkvPos qp[NIT];
-  bool fin[NIT];
-  int fm[NIT], fn[NIT];
-  unsigned xoff[NIT];
-  const int nt0 = tl.ng * NT;
+  const int t_ = wave / MT, q_ = wave - t_ * MT, nt = tl.ng * NT + t_, n0 = nt * 16 + (lane >> 4) * 4;
+  uint4 xin = uint4{0, 0, 0, 0};
+  u32x2 gn = {0, 0};
+  QkvPos qp{};
+  bool fin;
+  int m;
+  unsigned xoff;
   auto fin_loads = [&](int mg) {
-    const int mt0 = mg * MT;
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int tile = wave + it * kWaves, t = tile / MT, q = tile - t * MT;
-      fin[it] = tile < NT * MT && mt0 + q < MTT;
-      fn[it] = (nt0 + t) * 16 + (lane >> 4) * 4;
-      fm[it] = (mt0 + q) * 16 + (lane & 15);
-      xoff[it] = ((unsigned)((mt0 + q) * NP + nt0 + t) * 64u + lane) * 16u;
-      if (add && fin[it]) {
-        xin[it] = ldc16(make_rsrc(a.x[cur], (size_t)Mp * D * 4), xoff[it]);
-        gn[it] = gain_bits4(gain, fn[it]);
-      }
-      if (!SPLIT && kind == kStQkv && fin[it]) qp[it] = qkv_pos<D>(a, sm, fn[it], fm[it]);
-    }
+    const int mt = mg * MT + q_;
+    fin = wave < NT * MT && mt < MTT;
+    m = mt * 16 + (lane & 15);
+    xoff = ((unsigned)(mt * NP + nt) * 64u + lane) * 16u;
+    if (add && !SPLIT && fin) xin = ldc16(rx, xoff);
+    if (!SPLIT && kind == kStQkv && fin) qp = qkv_pos<D>(a, sm, n0, m);
   };
   // The weights are requested before the wait.  Wavefront 0 does the polling and its loads return
   // in order, so it asks for its share afterwards (they are in the L2 by then).
   uint4 wf[NT * KW];                                  // the weight fragments of this wavefront's share of a task
   const int kt0 = (SPLIT ? tl.ks * (KW * kWaves) : 0) + wave * KW;
-  if (wave != 0) { load_weights<NT, KW>(W, tl.ng * NT, KT, kt0, lane, wf); fin_loads(tl.mg0); }
+  auto early = [&]() {
+    load_weights<NT, KW>(W, tl.ng * NT, KT, kt0, lane, wf);
+    if (add && wave < NT * MT) gn = gain_bits4(gain, n0);
+    fin_loads(tl.mg0);
+  };
+  if (wave != 0) early();
   if (!wait()) return false;
-  if (wave == 0) { load_weights<NT, KW>(W, tl.ng * NT, KT, kt0, lane, wf); fin_loads(tl.mg0); }
+  if (wave == 0) early();
   uint4 rb[DEPTH][MT][2];
   unsigned boff[MT];
   auto request = [&](int i) {
 #pragma unroll
     for (int q = 0; q < MT; ++q) {
-      rb[i % DEPTH][q][0] = ldc16(rin, boff[q], i * 1024u);
-      rb[i % DEPTH][q][1] = ldc16(rin, boff[q], i * 1024u + in_lo);
+      rb[i % DEPTH][q][0] = ldc16(rin, boff[q], (i % KW) * 1024u);
+      rb[i % DEPTH][q][1] = ldc16(rin, boff[q], (i % KW) * 1024u + in_lo);
     }
   };
-  auto request_first = [&](int mg) {
+  auto aim = [&](int mg) {
 #pragma unroll
     for (int q = 0; q < MT; ++q) boff[q] = (unsigned)((min(mg * MT + q, MTT - 1) * KT + kt0) * 64 + lane) * 16u;
-#pragma unroll
-    for (int i = 0; i < DEPTH; ++i) request(i);
   };
-  request_first(tl.mg0);
+  // sixteen threads per row add up its square sums
+  uint4 ssv[(NP + 63) / 64];
+  const int srow = tid >> 4, sj = tid & 15;
+  const rsrc_t rs = make_rsrc(a.ssq[cur], (size_t)Mp * NP * 4);
+  const bool sums = normed && srow < MT * 16;
+  auto sum_loads = [&](int mg) {
+    const int mm = min(mg * (MT * 16) + srow, Mp - 1);
+#pragma unroll
+    for (int c = 0; c < NP; c += 64)
+      if (NP - c >= 64 || sj * 4 < NP - c) ssv[c / 64] = ldc16(rs, (unsigned)(mm * NP + c + sj * 4) * 4u);
+  };
+  aim(tl.mg0);
+#pragma unroll
+  for (int i = 0; i < DEPTH; ++i) request(i);
   const int claimed = claim();                        // (behind the requests: its wavefront's loads return in order)
-  for (int mg = tl.mg0; mg < tl.mg1; ++mg) {
-    const int mt0 = mg * MT;
-    // sixteen threads per row add up its square sums
-    uint4 ssv[MT == 4 ? 2 : 1][(NP + 63) / 64];
-    const int srow = tid >> 4, sj = tid & 15;
-    if (normed && (MT >= 2 || srow < MT * 16)) {
-      const rsrc_t rs = make_rsrc(a.ssq[cur], (size_t)Mp * NP * 4);
-#pragma unroll
-      for (int rr = 0; rr < (MT == 4 ? 2 : 1); ++rr) {
-        const int mm = min(mt0 * 16 + srow + rr * 32, Mp - 1);
-#pragma unroll
-        for (int c = 0; c < NP; c += 64)
-          if (NP - c >= 64 || sj * 4 < NP - c) ssv[rr][c / 64] = ldc16(rs, (unsigned)(mm * NP + c + sj * 4) * 4u);
-      }
-    }
-    if (mg == tl.mg0) warm_next<D>(a, sm, layer, st_no, wave, lane);   // (behind everything this group waits for)
-    f32x4 acc[NT][MT];
+  if (sums) sum_loads(tl.mg0);
+  warm_next<D>(a, sm, layer, st_no, wave, lane);      // (behind everything the first group waits for)
+
+  f32x4 acc[NT][MT];
+  // the products of one group; MORE: each slot of the ring is refilled for the following group
+  auto products = [&](auto MORE, int mg) {
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -446,100 +470,94 @@ __device__ __forceinline__ bool gemm_task(Smem& sm, const Wait& wait, const Clai
         for (int t = 0; t < NT; ++t)
           acc[t][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[t * KW + i]), bh, acc[t][q], 0, 0, 0);
       }
-      if (i + DEPTH < KW) request(i + DEPTH);
+      if (decltype(MORE)::value && i + DEPTH == KW) aim(mg + 1);
+      if (i + DEPTH < KW || decltype(MORE)::value) request(i + DEPTH);
     }
+  };
+  // Two sets of partial tiles, so that one barrier per group is enough: a wavefront that is through
+  // with a group goes on with the next one's products while others still finish tiles.
+  for (int mg = tl.mg0; mg < tl.mg1; ++mg) {
+    const int par = (mg - tl.mg0) & 1;
+    f32x4* const red = reinterpret_cast<f32x4*>(sm.red) + par * (kWaves * 8 * 64);
+    const bool more = !WHOLE && mg + 1 < tl.mg1;
+    if (more) products(std::true_type{}, mg); else products(std::false_type{}, mg);
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
       for (int q = 0; q < MT; ++q) red[(wave * (NT * MT) + t * MT + q) * 64 + lane] = acc[t][q];
-    if (normed && (MT >= 2 || srow < MT * 16)) {
+    if (sums) {
+      float x = 0.f;
 #pragma unroll
-      for (int rr = 0; rr < (MT == 4 ? 2 : 1); ++rr) {
-        float x = 0.f;
-#pragma unroll
-        for (int c = 0; c < NP; c += 64)
-          if (NP - c >= 64 || sj * 4 < NP - c) {
-            const float4 y = __builtin_bit_cast(float4, ssv[rr][c / 64]);
-            x += (y.x + y.y) + (y.z + y.w);
-          }
-        x += lane_xor<8>(x); x += lane_xor<4>(x); x += lane_xor<2>(x); x += lane_xor<1>(x);
-        if (sj == 0) sm.inv[srow + rr * 32] = 1.0f / sqrtf(x / (float)D + a.eps);
-      }
+      for (int c = 0; c < NP; c += 64)
+        if (NP - c >= 64 || sj * 4 < NP - c) {
+          const float4 y = __builtin_bit_cast(float4, ssv[c / 64]);
+          x += (y.x + y.y) + (y.z + y.w);
+        }
+      x += lane_xor<8>(x); x += lane_xor<4>(x); x += lane_xor<2>(x); x += lane_xor<1>(x);
+      if (sj == 0) sm.inv[par * 32 + srow] = 1.0f / sqrtf(x / (float)D + a.eps);
     }
     if (tid == kClaimer) sm.task = claimed;
     __syncthreads();
-    const bool more = mg + 1 < tl.mg1;
-    if (!SPLIT && more) request_first(mg + 1);
-    f32x4 v[NIT];
+    if (fin) {
+      f32x4 u = red[wave * 64 + lane];
 #pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int tile = wave + it * kWaves;
-      if (!fin[it]) continue;
-      v[it] = red[tile * 64 + lane];
-#pragma unroll
-      for (int k = 1; k < kWaves; ++k) v[it] += red[(k * (NT * MT) + tile) * 64 + lane];
-      if (normed) v[it] *= sm.inv[(tile % MT) * 16 + (lane & 15)];
-    }
-    bool finish = true;
-    if (SPLIT) {
-      const rsrc_t rp = make_rsrc(a.gpart, (size_t)Mp * D * 16);
-      const unsigned pk = (unsigned)Mp * D * 4u;      // bytes of one slice
-#pragma unroll
-      for (int it = 0; it < NIT; ++it)
-        if (fin[it]) stc16(rp, xoff[it] + tl.ks * pk, v[it]);
-      __builtin_amdgcn_s_waitcnt(0x0F70);
-      __syncthreads();
-      if (tid == 0) {
-        uint32_t* tk = a.gtickets + tl.ng * st.MG + mg;
-        const uint32_t old = __hip_atomic_fetch_add(tk, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sm.last = old == 3u;
-        if (old == 3u) st_coh(tk, 0u);
-      }
-      __syncthreads();
-      finish = uni(sm.last) != 0;
-      if (more) request_first(mg + 1);
-      if (finish) {
-#pragma unroll
-        for (int it = 0; it < NIT; ++it)
-          if (fin[it]) {
-            f32x4 s[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) s[k] = __builtin_bit_cast(f32x4, ldc16(rp, xoff[it], k * pk));
-            v[it] = ((s[0] + s[1]) + s[2]) + s[3];
-          }
-      }
-    }
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      if (!fin[it] || !finish) continue;
-      const int m = fm[it], n0 = fn[it];
-      f32x4 u = v[it];
-      if (!SPLIT && kind == kStQkv) {
+      for (int k = 1; k < kWaves; ++k) u += red[(k * (NT * MT) + wave) * 64 + lane];
+      if (normed) u *= sm.inv[par * 32 + q_ * 16 + (lane & 15)];
+      if (SPLIT) {
+        stc16(make_rsrc(a.gpart, (size_t)Mp * D * 16), xoff + tl.ks * ((unsigned)Mp * D * 4u), u);
+      } else if (kind == kStQkv) {
         f32x4 pr;
 #pragma unroll
         for (int e = 0; e < 4; ++e) pr[e] = lane_xor<32>(u[e]);
-        qkv_out<D>(a, w, make_rsrc(a.q, (size_t)a.M * D * 4), qp[it], m, u, pr);
-      } else if (!SPLIT && kind == kStCq) {
+        qkv_out<D>(a, w, make_rsrc(a.q, (size_t)a.M * D * 4), qp, m, u, pr);
+      } else if (kind == kStCq) {
         if (m < a.M) stc16(make_rsrc(a.q, (size_t)a.M * D * 4), ((unsigned)m * D + n0) * 4u, u);
-      } else if (!SPLIT && kind == kStUp) {
-        const rsrc_t ru = make_rsrc(a.U, (size_t)Mp * D * 16);
-        planes4<4 * D>(ru, (unsigned)Mp * D * 8u, m, n0, float4{gelu_erf_f(u[0]), gelu_erf_f(u[1]), gelu_erf_f(u[2]), gelu_erf_f(u[3])});
+      } else if (kind == kStUp) {
+        planes4<4 * D>(make_rsrc(a.U, (size_t)Mp * D * 16), (unsigned)Mp * D * 8u, m, n0,
+                       float4{gelu_erf_f(u[0]), gelu_erf_f(u[1]), gelu_erf_f(u[2]), gelu_erf_f(u[3])});
       } else {
-        u += __builtin_bit_cast(f32x4, xin[it]);
-        if (last) {                                   // the pass's result: fp32 rows
-          if (m < a.M) *reinterpret_cast<f32x4*>(a.x_out + (size_t)m * D + n0) = u;
-          continue;
-        }
-        const rsrc_t ro = make_rsrc(a.x[cur ^ 1], (size_t)Mp * D * 4), rp = make_rsrc(a.P[cur ^ 1], (size_t)Mp * D * 4);
-        stc16(ro, xoff[it], u);
-        const float4 g = gain4(gn[it]);
-        planes4<D>(rp, (unsigned)Mp * D * 2u, m, n0, float4{u[0] * g.x, u[1] * g.y, u[2] * g.z, u[3] * g.w});
-        float s = u[0] * u[0] + u[1] * u[1] + u[2] * u[2] + u[3] * u[3];
-        s += lane_xor<16>(s); s += lane_xor<32>(s);
-        if (lane < 16) st_coh(a.ssq[cur ^ 1] + (size_t)m * NP + (n0 >> 4), s);
+        add_out<D>(a, cur, last, m, n0, xoff, lane, u + __builtin_bit_cast(f32x4, xin), gain4(gn));
       }
     }
-    if (more) { fin_loads(mg + 1); __syncthreads(); } // (LDS is free)
+    if (more) {
+      fin_loads(mg + 1);
+      if (sums) sum_loads(mg + 1);
+    }
+  }
+  if (SPLIT) {
+    // the last of the four slices' tasks to get here adds them up, group by group
+    const rsrc_t rp = make_rsrc(a.gpart, (size_t)Mp * D * 16);
+    const unsigned pk = (unsigned)Mp * D * 4u;        // bytes of one slice
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    __syncthreads();
+    if (tid == 0) {
+      uint32_t* tk = a.gtickets + tl.ng * st.MC + tl.mc;
+      const uint32_t old = __hip_atomic_fetch_add(tk, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      sm.last = old == 3u;
+      if (old == 3u) st_coh(tk, 0u);
+    }
+    __syncthreads();
+    if (uni(sm.last) != 0 && wave < NT * MT) {
+      constexpr int B = 2;                            // groups requested together
+      for (int mg = tl.mg0; mg < tl.mg1; mg += B) {
+        f32x4 s[B][5];
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+          const int mt = min(min(mg + j, tl.mg1 - 1) * MT + q_, MTT - 1);
+          const unsigned o = ((unsigned)(mt * NP + nt) * 64u + lane) * 16u;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) s[j][k] = __builtin_bit_cast(f32x4, ldc16(rp, o, k * pk));
+          s[j][4] = __builtin_bit_cast(f32x4, ldc16(rx, o));
+        }
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+          const int mt = (mg + j) * MT + q_;
+          if (mg + j < tl.mg1 && mt < MTT)
+            add_out<D>(a, cur, last, mt * 16 + (lane & 15), n0, ((unsigned)(mt * NP + nt) * 64u + lane) * 16u, lane,
+                       (((s[j][0] + s[j][1]) + s[j][2]) + s[j][3]) + s[j][4], gain4(gn));
+        }
+      }
+    }
   }
   return true;
 }
@@ -811,6 +829,8 @@ __device__ __forceinline__ bool attn_task(Smem& sm, const Wait& wait, const Clai
   return true;
 }
 
+static_assert(sizeof(Smem) <= 160 * 1024, "one compute unit's LDS");
+
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(kThreads) void k_layers(const LayersArgs a) {
@@ -842,7 +862,7 @@ __global__ __launch_bounds__(kThreads) void k_layers(const LayersArgs a) {
     const LayerStage& st = a.stage[p.st];
     const int need = p.layer * a.per_layer + st.base;
     const bool att = st.kind == kStAtt || st.kind == kStCatt;
-    Tile tl{0, 0, 0, 0};
+    Tile tl{};
     const bool real = att || tile_pos(st, p.idx, &tl);
     // every task of the stages in front is done?
     auto wait = [&]() {
@@ -924,10 +944,10 @@ void layers_tile(int ntiles, int mtiles, int kbytes, bool down, LayerStage* st) 
     const int NG = ntiles / nt, MG = (mtiles + mt - 1) / mt;
     int MC = 256 / (NG * ks);                         // row chunks that still give one task per workgroup
     if (MC < 1) MC = 1;
-    if (MC > MG) MC = MG;
+    if (MC > MG || (down && ks == 1)) MC = MG;
     const int rounds = (NG * MC * ks + 255) / 256, groups = (MG + MC - 1) / MC;
     const double stream = (double)kbytes / ks * mt * 64 / 95e3 + 0.08 * nt * mt;
-    const double us = rounds * (1.9 + groups * stream + (ks > 1 ? 2.0 + 1.2 * (groups - 1) : 0.0) + 0.4 * (groups - 1));
+    const double us = rounds * (1.9 + groups * stream + (ks > 1 ? 2.0 + 0.5 * (groups - 1) : 0.0) + 0.4 * (groups - 1));
     if (us < best) { best = us; st->NT = nt; st->MT = mt; st->KS = ks; st->MC = MC; st->NG = NG; st->MG = MG; }
   }
 }
