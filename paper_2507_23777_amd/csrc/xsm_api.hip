@@ -88,7 +88,7 @@ void build_work_offsets(const xsm_ctx* c, bool step_only, WorkOff& w, size_t& ro
   n_tickets = attn_pairs;
   w.part = take(fattn_part_bytes(part_entries));
   w.tickets = take(attn_pairs * 4);
-  w.gpart = w.gtickets = 0;
+  w.gpart = w.gtickets = w.gpart_floats = 0;
   if (c->fast) {
     // partial products of the split-contraction GEMM, for the largest projection it may run
     const int shapes[6][2] = {{(int)(3 * d), (int)d}, {(int)d, (int)d}, {(int)F, (int)d}, {(int)d, (int)F},
@@ -103,6 +103,7 @@ void build_work_offsets(const xsm_ctx* c, bool step_only, WorkOff& w, size_t& ro
     if (need_dn > fl) fl = need_dn;
     if (need_o > fl) fl = need_o;
     w.gpart = take(fl * 4);
+    w.gpart_floats = fl;
     w.gtickets = take(kWsTickets * 4);
   }
   w.lctrl = w.lssq = w.lerr = 0;
@@ -386,6 +387,63 @@ void run_layers(xsm_ctx* c, LayersBegin b, bool kv_only, uint32_t* wflags, hipSt
   launch_layers(b, a, g.d_model, s);
 }
 
+// Large passes (more rows than the layers kernel takes): one launch per stage on the blocked
+// projections; the rows enter as in run_layers.
+bool tiled_usable(const xsm_ctx* c, int M) { return c->tile_ok && M > 256; }
+void run_tiled(xsm_ctx* c, LayersBegin b, bool kv_only, uint32_t* wflags, int len_bound, hipStream_t s) {
+  const xsm_config& g = c->cfg;
+  char* ws = c->d_ws;
+  const int d = g.d_model, F = g.d_ffn, n_seq = b.n_seq, R = b.R, M = n_seq * R;
+  const size_t Mp = ((size_t)M + 15) & ~(size_t)15;
+  float* x = (float*)(ws + c->ws.QKV);
+  float* ssq = x + Mp * d;
+  void* P = ws + c->ws.Xn;
+  void* AO = ws + c->ws.AO;
+  float* Qr = (float*)(ws + c->ws.Qr);
+  const int32_t* eff = (const int32_t*)(ws + c->ws.eff_len);
+  const int32_t* slot = (const int32_t*)(ws + c->ws.slot);
+  b.gain = (const uint16_t*)layer_ptrs(c, 0).g1;
+  b.eff_len = (int32_t*)(ws + c->ws.eff_len); b.slot_out = (int32_t*)(ws + c->ws.slot); b.wflags = wflags;
+  b.d = d; b.H = g.n_heads; b.x = x; b.planes = P; b.ssq = ssq;
+  launch_layers_begin(b, s);
+  TileGemm t0{};
+  t0.M = M; t0.eps = g.rms_eps; t0.x = x; t0.P = P; t0.ssq_out = ssq;
+  t0.rope = (const float2*)(c->d_w + c->rope_off); t0.eff_len = eff; t0.slot = slot;
+  t0.R = R; t0.H = g.n_heads; t0.cap = c->cap_self;
+  t0.part = (float*)(ws + c->ws.gpart); t0.tickets = (uint32_t*)(ws + c->ws.gtickets);
+  auto gemm = [&](int kind, size_t W, int N, int K, const void* A, bool normed, float* Y, const void* gain, bool last) {
+    TileGemm t = t0;
+    t.kind = kind; t.W = (const uint4*)(c->d_w + W); t.N = N; t.K = K; t.A = A; t.ssq_in = normed ? ssq : nullptr; t.Y = Y;
+    t.gain = (const uint16_t*)gain; t.x_out = last ? (float*)(ws + c->ws.X) : nullptr;
+    launch_gemm_tile(t, c->ws.gpart_floats, s);
+  };
+  for (int l = 0; l < g.n_layers; ++l) {
+    const LayerPtrs L = layer_ptrs(c, l);
+    const TiledLayer& T = c->toff.layer[l];
+    t0.Kc = (uint16_t*)self_cache(c, l, 0); t0.Vc = (uint16_t*)self_cache(c, l, 1);
+    gemm(kTileQkv, T.Wqkv, 3 * d, d, P, true, Qr, nullptr, false);
+    if (kv_only && l == g.n_layers - 1) break;        // the cache is all that is wanted
+    FastAttn a{};
+    a.Q = Qr; a.ldq = d; a.Kc = t0.Kc; a.Vt = t0.Vc; a.eff_len = eff; a.slot = slot; a.O = (float*)AO; a.ldo = d;
+    a.part = (float*)(ws + c->ws.part); a.tickets = (uint32_t*)(ws + c->ws.tickets);
+    a.R = R; a.H = g.n_heads; a.cap = c->cap_self; a.S = attn_splits(c, n_seq * ((R + 15) / 16), len_bound + R); a.fixed_limit = 0;
+    a.scale_log2 = 1.4426950408889634f / sqrtf((float)g.head_dim); a.o_planes = 1; a.o_rows = M;
+    launch_fattn(a, n_seq, s);
+    gemm(kTileAdd, T.Wo, d, d, AO, false, nullptr, g.n_cond > 0 ? L.gc : L.g2, false);
+    if (g.n_cond > 0) {
+      gemm(kTileStore, T.Wcq, d, d, P, true, Qr, nullptr, false);
+      FastAttn ca = a;
+      ca.Kc = (const uint16_t*)cross_cache(c, l, 0); ca.Vt = (const uint16_t*)cross_cache(c, l, 1);
+      ca.cap = c->cap_cross; ca.fixed_limit = g.n_cond; ca.S = attn_splits(c, n_seq * ((R + 15) / 16), g.n_cond);
+      launch_fattn(ca, n_seq, s);
+      gemm(kTileAdd, T.Wco, d, d, AO, false, nullptr, L.g2, false);
+    }
+    gemm(kTileGelu, T.W1, F, d, P, true, (float*)(ws + c->ws.U), nullptr, false);
+    const bool last = l == g.n_layers - 1;
+    gemm(kTileAdd, T.W2, d, F, ws + c->ws.U, false, nullptr, last ? nullptr : layer_ptrs(c, l + 1).g1, last);
+  }
+}
+
 // attention's arrival counters in the bound workspace start at zero (and return to zero in every pass)
 void clear_tickets(xsm_ctx* ctx, hipStream_t s) {
   const xsm_config& g = ctx->cfg;
@@ -495,6 +553,11 @@ int step_common(xsm_ctx* ctx, const xsm_batch* bt, const xsm_verify_params* vp, 
     b.E = (const uint16_t*)(wb + ctx->woff.E * e); b.block = bt->block; b.kv_len = bt->kv_len; b.slot = bt->slot;
     b.n_seq = n_seq; b.R = R; b.vocab = V; b.max_batch = g.max_batch; b.max_ctx = g.max_ctx; b.bound = bt->kv_len_bound;
     run_layers(ctx, b, false, wfl, s);
+  } else if (tiled_usable(ctx, M)) {
+    LayersBegin b{};
+    b.E = (const uint16_t*)(wb + ctx->woff.E * e); b.block = bt->block; b.kv_len = bt->kv_len; b.slot = bt->slot;
+    b.n_seq = n_seq; b.R = R; b.vocab = V; b.max_batch = g.max_batch; b.max_ctx = g.max_ctx; b.bound = bt->kv_len_bound;
+    run_tiled(ctx, b, false, wfl, bt->kv_len_bound, s);
   } else {
     launch_prepare(bt->kv_len, bt->slot, bt->block, n_seq, R, V, g.max_batch, g.max_ctx,
                    bt->kv_len_bound, eff, slot, wfl, s);
@@ -634,6 +697,7 @@ int xsm_create(const xsm_config* cfg, xsm_ctx** out) {
             g.vocab % 16 == 0;
   c->small_ok = c->fast && g.n_cond == 0 && small_supported(g.d_model, g.d_ffn) && g.vocab <= 65536 &&
                 g.n_layers <= 48;
+  c->tile_ok = c->fast && tile_supported(g.d_model, g.d_ffn, g.n_heads);
   c->layers_ok = c->fast && layers_supported(g.d_model, g.d_ffn, g.n_layers);
   build_weight_offsets(c);
   {
@@ -864,11 +928,13 @@ int xsm_prefill(xsm_ctx* ctx, int32_t n_seq, const int32_t* h_slot, const void* 
   }
   for (int r0 = 0; r0 < P; r0 += chunk) {
     const int C = P - r0 < chunk ? P - r0 : chunk;
-    if (ctx->layers_ok && !ctx->layers_failed && layers_usable(n_seq, C)) {
+    const bool persistent = ctx->layers_ok && !ctx->layers_failed && layers_usable(n_seq, C);
+    if (persistent || tiled_usable(ctx, n_seq * C)) {
       LayersBegin b{};
       b.rows = (const uint16_t*)d_prefix_emb; b.rows_per_seq = P; b.row0 = r0;
       b.n_seq = n_seq; b.R = C;
-      run_layers(ctx, b, true, nullptr, s);
+      if (persistent) run_layers(ctx, b, true, nullptr, s);
+      else run_tiled(ctx, b, true, nullptr, r0, s);
       continue;
     }
     launch_fill_i32(eff, n_seq, r0, s);

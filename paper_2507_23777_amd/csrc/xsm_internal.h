@@ -35,6 +35,7 @@ struct WorkOff {
   size_t part, tickets, gpart, gtickets;                                  // split-key attention partials
   size_t ll, ctrl, head_all, tlog;                       // single-launch step: exchange buffers
   size_t lctrl, lssq, lerr;                              // persistent layers kernel: queues and partition, square sums, error word
+  size_t gpart_floats;                                   // size of gpart
   size_t total;
 };
 
@@ -91,6 +92,7 @@ struct xsm_ctx {
   bool small_failed = false;   // xsm_check_device found a timed-out wait: per-stage kernels until weights are loaded again
   bool gemm_unmatched = false; // a projection found no kernel for its (prologue, epilogue) pair: the step reports it
   bool layers_failed = false;  // xsm_check_device found a timed-out wait of it: per-stage kernels until weights are loaded again
+  bool tile_ok = false;    // row- and column-blocked projections of large passes available for this model shape
   bool layers_ok = false;  // persistent layers kernel available for this model shape
   size_t layer_wts_off = 0;              // byte offset of the LayerWts array in the weights buffer
   std::vector<xsm::LayerWts> layer_wts;  // host copy (source of the upload)
@@ -253,6 +255,7 @@ struct LayersBegin {
   const uint16_t* gain;                 // first norm
   int n_seq, R, d, H, vocab, max_batch, max_ctx, bound;
   int32_t* eff_len; int32_t* slot_out; uint32_t* wflags;
+  int partition;                        // 1: also attention's shares and cleared queues (xsm_layers.hip)
   float* x; void* planes; float* ssq; uint32_t* ctrl; int32_t* unit_pre;                 // (set by launch_layers)
 };
 struct LayersArgs {
@@ -274,6 +277,26 @@ bool layers_usable(int n_seq, int R);
 size_t layers_ctrl_bytes();
 size_t layers_part_bytes();
 void launch_layers(LayersBegin b, LayersArgs a, int D, hipStream_t s);
+void launch_layers_begin(const LayersBegin& b, hipStream_t s);
+
+// ---- projections of large passes (xsm_gemm_tile.hip) ------------------------------------
+enum { kTileQkv = 0, kTileStore, kTileGelu, kTileAdd };
+struct TileGemm {
+  const uint4* W;              // fragment-ordered weights [N/16][K/32][64]
+  const void* A;               // bf16 hi / lo operand planes [M][K]
+  int M, N, K, kind;
+  const float* ssq_in; float eps;        // square sums [M][K/16] of the rows the planes come from: scale by 1 / rms (nullptr: don't)
+  float* Y;                    // kTileQkv: rotated queries [M][K]; kTileStore: rows [M][N]; kTileGelu: operand planes [M][N]
+  // kTileAdd: residual in tile order (updated), planes of (residual x gain), their square sums; x_out: fp32 rows instead
+  float* x; float* x_out; const uint16_t* gain; void* P; float* ssq_out;
+  // kTileQkv
+  const float2* rope; const int32_t* eff_len; const int32_t* slot; uint16_t* Kc; uint16_t* Vc;
+  int R, H, cap;
+  // slices of the contraction (set by the launcher)
+  int KS; float* part; uint32_t* tickets;
+};
+bool tile_supported(int d, int F, int H);
+void launch_gemm_tile(TileGemm g, size_t part_floats, hipStream_t s);
 
 // ---- single-launch step for <= 16 block rows (xsm_step_small.hip) -------------------
 struct SmallArgs {

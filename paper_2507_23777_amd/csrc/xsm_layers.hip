@@ -166,7 +166,8 @@ __global__ __launch_bounds__(256) void k_layers_begin(const LayersBegin a) {
   }
   __shared__ int cnt[kMaxUnits];
   const int QT = (a.R + 15) >> 4, NU = a.n_seq * QT;
-  for (int i = tid; i < 2 * kQueues * kQueueStride; i += 256) a.ctrl[i] = 0;
+  if (a.partition)
+    for (int i = tid; i < 2 * kQueues * kQueueStride; i += 256) a.ctrl[i] = 0;
   for (int b = tid; b < a.n_seq; b += 256) {
     int len = a.row0, sl = 0;
     if (!a.rows) {
@@ -176,9 +177,10 @@ __global__ __launch_bounds__(256) void k_layers_begin(const LayersBegin a) {
       a.wflags[b] = f;
     }
     a.eff_len[b] = len;
-    for (int qt = 0; qt < QT; ++qt)
+    for (int qt = 0; a.partition && qt < QT; ++qt)
       cnt[b * QT + qt] = len < 0 ? 0 : (len + min(a.R, (qt + 1) * 16) + 63) >> 6;
   }
+  if (!a.partition) return;
   __syncthreads();
   // exclusive prefix sums of the units' chunk counts: a run of units per thread, then over the runs
   __shared__ int tot[256];
@@ -962,6 +964,10 @@ bool layers_usable(int n_seq, int R) {
 size_t layers_ctrl_bytes() { return (size_t)2 * kQueues * kQueueStride * 4 + (size_t)(kMaxUnits + 64) * 4; }
 size_t layers_part_bytes() { return (size_t)kTasksPerAttn * 2 * kSlotFloats * 4; }
 
+void launch_layers_begin(const LayersBegin& b, hipStream_t s) {
+  hipLaunchKernelGGL(k_layers_begin, dim3(b.n_seq * b.R + 1), dim3(256), 0, s, b);
+}
+
 void launch_layers(LayersBegin b, LayersArgs a, int D, hipStream_t s) {
   TraceScope trace_("fattn", s);               // (its kernel class: attention and everything between)
   const int M = b.n_seq * b.R;
@@ -987,7 +993,8 @@ void launch_layers(LayersBegin b, LayersArgs a, int D, hipStream_t s) {
   if (a.n_cond > 0) { gemm(kStCq, D / 16, D); attn(kStCatt); gemm(kStCo, D / 16, D); }
   gemm(kStUp, 4 * D / 16, D); gemm(kStDown, D / 16, 4 * D);
   a.n_stages = ns; a.per_layer = base; a.adds = adds;
-  hipLaunchKernelGGL(k_layers_begin, dim3(M + 1), dim3(256), 0, s, b);
+  b.partition = 1;
+  launch_layers_begin(b, s);
   auto go = [&](auto kfn) {
     allow_dynamic_lds((const void*)kfn, sizeof(Smem));
     hipLaunchKernelGGL(kfn, dim3(256), dim3(kThreads), sizeof(Smem), s, a);
