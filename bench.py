@@ -74,11 +74,14 @@ def cpu_baseline(cfg: dict, w: dict, prefix, first, budget_s: float = 15.0) -> d
                       f"(context {cfg['prefix']}..{st.n}), float64 numpy"}
 
 
-def projection_flops(cfg: dict, M: int, n_seq: int) -> float:
+def projection_flops(cfg: dict, M: int, n_seq: int, layers: bool = True) -> float:
     """Useful multiply-adds x 2 of one speculative step's projections over M block rows (every
-    weight matrix once per row; the decoding heads and their unembedding run on n_seq x K rows)."""
+    weight matrix once per row; the decoding heads and their unembedding run on n_seq x K rows).
+    layers=False: without those of the layers."""
     L, d, F, V, K = cfg["n_layers"], cfg["d_model"], cfg["d_ffn"], cfg["vocab"], cfg["n_draft"]
     cross = 2 * d * d if cfg["n_cond"] else 0
+    if not layers:
+        L = 0
     return 2.0 * (M * (L * (4 * d * d + 2 * d * F + cross) + V * d) + n_seq * K * (d * d + V * d))
 
 
@@ -121,7 +124,10 @@ def measure_point(name, B, K, ctx, steps, warmup, torch, pkg, xsm, si, max_ctx=N
     cfgb = dict(cfg, n_draft=R - 1)
     by = algorithmic_bytes(cfgb, B, B * ctx)
     gemm_ms = sum(v[1] for k, v in trace.items() if k.startswith("gemm") or k == "fgemm") / steps
-    fl = projection_flops(cfgb, B * R, B)
+    # all layers as one launch (its trace class is attention's, once per step): the projection launches
+    # are then those behind the layers
+    one_launch = trace.get("fattn", (0,))[0] < steps * cfg["n_layers"]
+    fl = projection_flops(cfgb, B * R, B, layers=not one_launch)
     dom = max(trace.items(), key=lambda kv: kv[1][1])[0]
     out = {"workload": f"{name} batch {B} K={R - 1}{' plain step' if plain else ''} context {ctx}", "steps": steps,
            "ms_per_step": round(ms, 4), "verified_tok_per_s": round(B * R / ms * 1e3, 1),
@@ -132,7 +138,9 @@ def measure_point(name, B, K, ctx, steps, warmup, torch, pkg, xsm, si, max_ctx=N
         tf = fl / (gemm_ms * 1e-3) / 1e12
         out["projections"] = {"ms_per_step": round(gemm_ms, 4), "useful_tflops": round(tf, 1),
                               "frac_of_mfma_bf16_peak": round(tf / MFMA_BF16_PEAK_TFLOPS, 4),
-                              "note": "useful flops of all projection GEMMs / their summed launch time (event pairs); every "
+                              "note": ("useful flops of the projection GEMMs behind the layers (those inside run in the layers' "
+                                       "one launch)" if one_launch else "useful flops of all projection GEMMs") +
+                                      " / their summed launch time (event pairs); every "
                                       "product is issued twice (hi and lo operand halves of an fp32 activation), so the "
                                       "matrix cores issue twice this"}
     eng.close()
