@@ -78,8 +78,7 @@ void build_work_offsets(const xsm_ctx* c, bool step_only, WorkOff& w, size_t& ro
   w.Zh = take((size_t)g.max_batch * (K ? K : 1) * V * 4);
   w.eff_len = take(g.max_batch * 4); w.slot = take(g.max_batch * 4); w.acc = take(g.max_batch * 4);
   w.y0 = take(g.max_batch * 4); w.wflags = take(g.max_batch * 4);
-  w.toks = take((size_t)g.max_batch * kMaxRows * 4);
-  w.rowidx = take(g.max_batch * 4);
+  w.rowidx = take(g.max_batch * 4); w.arrived = take(g.max_batch * 4);
   w.eff2 = take((size_t)g.max_batch * (K ? K : 1) * 4); w.slot2 = take((size_t)g.max_batch * (K ? K : 1) * 4);
   // (sequence, head) pairs of one attention call: the backbone's, or all cross-attention decoding heads at once
   size_t attn_pairs = (size_t)g.max_batch * g.n_heads * (g.head_kind == XSM_HEAD_CA && K ? K : 1);
@@ -505,6 +504,9 @@ int step_common(xsm_ctx* ctx, const xsm_batch* bt, const xsm_verify_params* vp, 
   int32_t* slot = (int32_t*)(ws + ctx->ws.slot);
   int32_t* acc = (int32_t*)(ws + ctx->ws.acc);
   int32_t* y0 = (int32_t*)(ws + ctx->ws.y0);
+  int32_t* rowidx = (int32_t*)(ws + ctx->ws.rowidx);
+  int32_t* words = (int32_t*)(ws + ctx->ws.part);          // attention's partials (4 KB per sequence at least), free between its launches
+  uint32_t* tick = (uint32_t*)(ws + ctx->ws.arrived);      // cleared in front of every step, with its inputs' validation
   uint32_t* wfl = (uint32_t*)(ws + ctx->ws.wflags);
   const char* wb = ctx->d_w;
   const size_t e = ctx->esz;
@@ -552,15 +554,17 @@ int step_common(xsm_ctx* ctx, const xsm_batch* bt, const xsm_verify_params* vp, 
     LayersBegin b{};
     b.E = (const uint16_t*)(wb + ctx->woff.E * e); b.block = bt->block; b.kv_len = bt->kv_len; b.slot = bt->slot;
     b.n_seq = n_seq; b.R = R; b.vocab = V; b.max_batch = g.max_batch; b.max_ctx = g.max_ctx; b.bound = bt->kv_len_bound;
+    b.arrived = tick;
     run_layers(ctx, b, false, wfl, s);
   } else if (tiled_usable(ctx, M)) {
     LayersBegin b{};
     b.E = (const uint16_t*)(wb + ctx->woff.E * e); b.block = bt->block; b.kv_len = bt->kv_len; b.slot = bt->slot;
     b.n_seq = n_seq; b.R = R; b.vocab = V; b.max_batch = g.max_batch; b.max_ctx = g.max_ctx; b.bound = bt->kv_len_bound;
+    b.arrived = tick;
     run_tiled(ctx, b, false, wfl, bt->kv_len_bound, s);
   } else {
     launch_prepare(bt->kv_len, bt->slot, bt->block, n_seq, R, V, g.max_batch, g.max_ctx,
-                   bt->kv_len_bound, eff, slot, wfl, s);
+                   bt->kv_len_bound, eff, slot, wfl, tick, s);
     launch_embed(dt, wb + ctx->woff.E * e, bt->block, eff, X, n_seq, R, d, s);
     forward_blocks(ctx, n_seq, R, bt->kv_len_bound, s);
   }
@@ -572,18 +576,16 @@ int step_common(xsm_ctx* ctx, const xsm_batch* bt, const xsm_verify_params* vp, 
     z.Y = Z0; z.ldy = V; z.nscratch = Xn; z.ws_part = gpart; z.ws_tickets = gtick; z.pend = PEND;
     fgemm(ctx, PRO_NORM, FEPI_STORE, z, s);
     if (bt->logits_dbg) launch_copy_f32(Z0, bt->logits_dbg, (size_t)M * V, s);
-    launch_verify(Z0, nullptr, bt->block, eff, slot, *vp, acc, y0, wfl, nullptr, n_seq, R, V, d, s);
+    launch_verify(Z0, nullptr, bt->block, eff, slot, *vp, acc, y0, wfl, rowidx, words, tick, nullptr, n_seq, R, V, d, s);
     if (K > 0 && g.head_kind == XSM_HEAD_CA) {
       // Eq. 4 with cross-attention heads, all heads of all sequences at once: q = Wq_k g (one
       // stacked GEMM), one attention call over the heads' cached condition keys/values with
       // (sequence, head) as the batch index, then per head the output projection onto the
       // residual g and the head's own unembedding.
-      int32_t* rowidx = (int32_t*)(ws + ctx->ws.rowidx);
       int32_t* eff2 = (int32_t*)(ws + ctx->ws.eff2);
       int32_t* slot2 = (int32_t*)(ws + ctx->ws.slot2);
       float* Qh = Hh;                                        // [n_seq][K][d]
       float* Oh = (float*)(ws + ctx->ws.Qr);                 // [n_seq][K][d]
-      launch_head_rows(acc, rowidx, n_seq, R, s);
       launch_norm_rows(X, d, rowidx, z.gain, g.rms_eps, G, n_seq, d, s);
       launch_head_ca_prep(G, Rk, eff, slot, eff2, slot2, n_seq, K, d, g.max_batch, s);
       FastGemm hq{};
@@ -612,8 +614,6 @@ int step_common(xsm_ctx* ctx, const xsm_batch* bt, const xsm_verify_params* vp, 
       }
       if (bt->head_logits_dbg) launch_copy_f32(Zh, bt->head_logits_dbg, (size_t)n_seq * K * V, s);
     } else if (K > 0) {
-      int32_t* rowidx = (int32_t*)(ws + ctx->ws.rowidx);
-      launch_head_rows(acc, rowidx, n_seq, R, s);
       FastGemm hg{};                               // all K heads at once: [K*d][d] stacked
       hg.Wt = (const uint4*)(wb + ctx->toff.Wh); hg.N = K * d; hg.K = d; hg.M = n_seq;
       hg.X = X; hg.ldx = d; hg.gain = z.gain; hg.eps = g.rms_eps; hg.row_index = rowidx;
@@ -630,8 +630,8 @@ int step_common(xsm_ctx* ctx, const xsm_batch* bt, const xsm_verify_params* vp, 
     launch_rmsnorm(dt, X, wb + ctx->woff.gf * e, Xn, M, d, g.rms_eps, s);            // Hf
     launch_gemm(dt, EPI_STORE, Xn, d, wb + ctx->woff.WU * e, Z0, V, M, V, d, s);      // Eq. 3 logits
     if (bt->logits_dbg) launch_copy_f32(Z0, bt->logits_dbg, (size_t)M * V, s);
-    launch_verify(Z0, Xn, bt->block, eff, slot, *vp, acc, y0, wfl, K > 0 ? G : nullptr, n_seq, R, V,
-                  d, s);
+    launch_verify(Z0, Xn, bt->block, eff, slot, *vp, acc, y0, wfl, nullptr, words, tick, K > 0 ? G : nullptr, n_seq, R,
+                  V, d, s);
     if (K > 0 && g.head_kind == XSM_HEAD_CA) {
       int32_t* eff2 = (int32_t*)(ws + ctx->ws.eff2);
       int32_t* slot2 = (int32_t*)(ws + ctx->ws.slot2);
@@ -661,7 +661,7 @@ int step_common(xsm_ctx* ctx, const xsm_batch* bt, const xsm_verify_params* vp, 
       if (bt->head_logits_dbg) launch_copy_f32(Zh, bt->head_logits_dbg, (size_t)n_seq * K * V, s);
     }
   }
-  launch_emit(Zh, *vp, eff, slot, acc, y0, wfl, (int32_t*)(ws + ctx->ws.toks), bt->block, bt->kv_len, bt->out_tokens,
+  launch_emit(Zh, *vp, eff, slot, acc, y0, wfl, words, tick, bt->block, bt->kv_len, bt->out_tokens,
               bt->n_accepted, bt->flags, n_seq, R, K, V, s);
   hipError_t e2 = hipGetLastError();
   if (e2 != hipSuccess) return fail(ctx, XSM_EHIP, std::string("launch: ") + hipGetErrorString(e2));

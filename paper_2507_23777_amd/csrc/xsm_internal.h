@@ -31,7 +31,7 @@ struct WeightOff {
 // Byte offsets inside the caller's workspace buffer.
 struct WorkOff {
   size_t X, Xn, QKV, Qr, AO, U, Z0, G, Hh, Rk, Zh;
-  size_t eff_len, slot, acc, y0, wflags, toks, rowidx, eff2, slot2;   // int32 arrays
+  size_t eff_len, slot, acc, y0, wflags, rowidx, arrived, eff2, slot2;   // int32 arrays
   size_t part, tickets, gpart, gtickets;                                  // split-key attention partials
   size_t ll, ctrl, head_all, tlog;                       // single-launch step: exchange buffers
   size_t lctrl, lssq, lerr;                              // persistent layers kernel: queues and partition, square sums, error word
@@ -153,7 +153,7 @@ void launch_rope_table(float2* tab, int max_ctx, int head_dim, float theta, hipS
 // flag bits.
 void launch_prepare(const int32_t* kv_len, const int32_t* slot, const int32_t* block, int n_seq,
                     int R, int vocab, int max_batch, int max_ctx, int kv_len_bound,
-                    int32_t* eff_len, int32_t* slot_out, uint32_t* wflags, hipStream_t s);
+                    int32_t* eff_len, int32_t* slot_out, uint32_t* wflags, uint32_t* arrived, hipStream_t s);
 void launch_fill_i32(int32_t* p, int n, int32_t v, hipStream_t s);
 
 void launch_embed(int dtype, const void* E, const int32_t* block, const int32_t* eff_len, float* X,
@@ -236,8 +236,6 @@ struct FastAttn {
 };
 void launch_fattn(const FastAttn& a, int n_seq, hipStream_t s);
 size_t fattn_part_bytes(size_t entries);
-// row_index[b] = b*R + acc[b] (the hidden state the decoding heads read)
-void launch_head_rows(const int32_t* acc, int32_t* row_index, int n_seq, int R, hipStream_t s);
 void launch_head_ca_prep(const float* G, float* Rk, const int32_t* eff, const int32_t* slot, int32_t* eff2,
                          int32_t* slot2, int n_seq, int K, int d, int max_batch, hipStream_t s);
 // out[m][:] = RMSNorm(X[row_index ? row_index[m] : m][:]) * gain (fp32 in and out, bf16 gain)
@@ -255,6 +253,7 @@ struct LayersBegin {
   const uint16_t* gain;                 // first norm
   int n_seq, R, d, H, vocab, max_batch, max_ctx, bound;
   int32_t* eff_len; int32_t* slot_out; uint32_t* wflags;
+  uint32_t* arrived;                    // decoding: counters of the step's tail, one per sequence, cleared
   int partition;                        // 1: also attention's shares and cleared queues (xsm_layers.hip)
   float* x; void* planes; float* ssq; uint32_t* ctrl; int32_t* unit_pre;                 // (set by launch_layers)
 };
@@ -331,14 +330,17 @@ void launch_gather_head_dbg(const float* head_all, const int32_t* acc, float* ou
                             int K, int V, hipStream_t s);
 
 // ---- launchers (xsm_kernels_verify.hip) --------------------------------------
+constexpr int kTailWords = 128;      // scratch words of a sequence (words: [n_seq][kTailWords]); tickets: [n_seq] zeros, zero again
+                                     // after each kernel
 void launch_verify(const float* Z0, const float* Hf, const int32_t* block, const int32_t* eff_len,
                    const int32_t* slot, const xsm_verify_params& vp, int32_t* acc, int32_t* y0,
-                   uint32_t* wflags, float* G, int n_seq, int R, int V, int d, hipStream_t s);
+                   uint32_t* wflags, int32_t* row_index /*optional: b*R + accepted*/, int32_t* words, uint32_t* tickets, float* G,
+                   int n_seq, int R, int V, int d, hipStream_t s);
 void launch_head_act(int dtype, const float* G, const float* Hh, const void* const* bias_ptrs,
                      float* Rk, int n_seq, int K, int d, hipStream_t s);
 void launch_emit(const float* Zh, const xsm_verify_params& vp, const int32_t* eff_len,
                  const int32_t* slot, const int32_t* acc, const int32_t* y0,
-                 uint32_t* wflags, int32_t* drawn /*[n_seq][16] scratch*/, int32_t* block, int32_t* kv_len,
+                 const uint32_t* wflags, int32_t* words, uint32_t* tickets, int32_t* block, int32_t* kv_len,
                  int32_t* out_tokens, int32_t* n_accepted, uint32_t* flags, int n_seq, int R, int K, int V,
                  hipStream_t s);
 void launch_copy_f32(const float* src, float* dst, size_t n, hipStream_t s);

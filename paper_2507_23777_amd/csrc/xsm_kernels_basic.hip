@@ -30,7 +30,7 @@ void launch_rope_table(float2* tab, int max_ctx, int head_dim, float theta, hipS
 // ---------------------------------------------------------------------------
 __global__ void k_prepare(const int32_t* kv_len, const int32_t* slot, const int32_t* block,
                           int n_seq, int R, int vocab, int max_batch, int max_ctx, int bound,
-                          int32_t* eff_len, int32_t* slot_out, uint32_t* wflags) {
+                          int32_t* eff_len, int32_t* slot_out, uint32_t* wflags, uint32_t* arrived) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= n_seq) return;
   uint32_t f = 0;
@@ -44,13 +44,14 @@ __global__ void k_prepare(const int32_t* kv_len, const int32_t* slot, const int3
   eff_len[b] = f ? -1 : n;
   slot_out[b] = (f & XSM_FLAG_BAD_SLOT) ? 0 : sl;
   wflags[b] = f;
+  arrived[b] = 0;                                      // (the tail's arrival counters)
 }
 void launch_prepare(const int32_t* kv_len, const int32_t* slot, const int32_t* block, int n_seq,
                     int R, int vocab, int max_batch, int max_ctx, int kv_len_bound,
-                    int32_t* eff_len, int32_t* slot_out, uint32_t* wflags, hipStream_t s) {
+                    int32_t* eff_len, int32_t* slot_out, uint32_t* wflags, uint32_t* arrived, hipStream_t s) {
   TraceScope trace_("prepare", s);
   hipLaunchKernelGGL(k_prepare, dim3((n_seq + 63) / 64), dim3(64), 0, s, kv_len, slot, block, n_seq,
-                     R, vocab, max_batch, max_ctx, kv_len_bound, eff_len, slot_out, wflags);
+                     R, vocab, max_batch, max_ctx, kv_len_bound, eff_len, slot_out, wflags, arrived);
 }
 
 __global__ void k_fill_i32(int32_t* p, int n, int32_t v) {
@@ -473,15 +474,6 @@ __global__ void k_gather_head_dbg(const float* head_all, const int32_t* acc, flo
 void launch_gather_head_dbg(const float* head_all, const int32_t* acc, float* out, int n_seq, int R,
                             int K, int V, hipStream_t s) {
   hipLaunchKernelGGL(k_gather_head_dbg, dim3(4, n_seq, K), dim3(256), 0, s, head_all, acc, out, R, K, V);
-}
-
-__global__ void k_head_rows(const int32_t* acc, int32_t* row_index, int n_seq, int R) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b < n_seq) row_index[b] = b * R + (acc[b] < 0 ? 0 : acc[b]);
-}
-void launch_head_rows(const int32_t* acc, int32_t* row_index, int n_seq, int R, hipStream_t s) {
-  TraceScope trace_("head_rows", s);
-  hipLaunchKernelGGL(k_head_rows, dim3((n_seq + 63) / 64), dim3(64), 0, s, acc, row_index, n_seq, R);
 }
 
 // Cross-attention heads: residual rows Rk[b][k][:] = G[b][:] and the (sequence, head) -> cache

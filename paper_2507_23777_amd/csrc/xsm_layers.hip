@@ -175,6 +175,7 @@ __global__ __launch_bounds__(256) void k_layers_begin(const LayersBegin a) {
       if (f) len = -1;
       a.slot_out[b] = sl;
       a.wflags[b] = f;
+      a.arrived[b] = 0;
     }
     a.eff_len[b] = len;
     for (int qt = 0; a.partition && qt < QT; ++qt)
