@@ -214,9 +214,11 @@ XSM_API int xsm_spec_step_static(xsm_ctx* ctx, const xsm_batch* batch, const xsm
 /* Options.  XSM_OPT_SINGLE_LAUNCH (default 1): when a step has at most 16 block rows in total,
  * the model shape is supported and the device has 256 compute units, run the whole step (backbone,
  * heads, unembedding, verification under any criterion, draws under any sampling rule, emit) as
- * one persistent kernel instead of one kernel per stage; 0 forces the per-stage kernels.  XSM_OPT_ATTN_SPLITS (tuning aid, default 0 = automatic): key-range slices per
- * (sequence, head) of the attention kernel / stage (the single-launch step takes the largest power
- * of two not above it).  XSM_OPT_PREFILL_ROWS (tuning aid, default 0 = as many as the workspace
+ * one persistent kernel instead of one kernel per stage; 0 forces the per-stage kernels.  (Passes of
+ * 17 to 1280 rows of a supported shape run all their layers as one persistent kernel of their own,
+ * whatever this option says.)  XSM_OPT_ATTN_SPLITS (tuning aid, default 0 = automatic): key-range
+ * slices per (sequence, head) of the attention kernel / stage (the single-launch step takes the
+ * largest power of two not above it; the layers kernel deals the keys out by itself).  XSM_OPT_PREFILL_ROWS (tuning aid, default 0 = as many as the workspace
  * holds, 8192): upper limit of the rows (sequences x positions) one prefill pass takes. */
 enum { XSM_OPT_SINGLE_LAUNCH = 1, XSM_OPT_TIMELINE = 2, XSM_OPT_ATTN_SPLITS = 3, XSM_OPT_PREFILL_ROWS = 4 };
 XSM_API int xsm_set_option(xsm_ctx* ctx, int32_t option, int32_t value);
@@ -227,15 +229,16 @@ XSM_API int xsm_set_option(xsm_ctx* ctx, int32_t option, int32_t value);
 XSM_API int xsm_debug_timeline(xsm_ctx* ctx, uint64_t* h_out, size_t n_words);
 
 /* Synchronises the device and reports whether a bounded device-side wait of the
- * single-launch step gave up since the last call (XSM_EDEVICE, reported once).  The step in
- * which that happened, and every single-launch step enqueued after it, wrote n_accepted[b] = 0
+ * single-launch step or of the layers kernel (a step's, or a prefill's) gave up since the last
+ * call (XSM_EDEVICE, reported once).  The step in which that happened, and every step enqueued
+ * after it (after a single-launch one: every single-launch step), wrote n_accepted[b] = 0
  * and XSM_FLAG_DEVICE_TIMEOUT for the sequences it could not finish and left their block,
  * kv_len and out_tokens untouched, so a caller that reads a step's outputs sees the failure
  * without this call.  After the report this context's steps run on the per-stage kernels
  * (until weights are loaded again): repeat the lost step.  XSM_OK otherwise. */
 XSM_API int xsm_check_device(xsm_ctx* ctx);
 
-/* Test only, synchronous: set the single-launch step's device-side error word as a timed-out
+/* Test only, synchronous: set the persistent kernels' device-side error words as a timed-out
  * wait would (no wait is made to spin), so that the failure path above can be exercised. */
 XSM_API int xsm_debug_inject_device_error(xsm_ctx* ctx, uint32_t code);
 

@@ -105,11 +105,10 @@ void build_work_offsets(const xsm_ctx* c, bool step_only, WorkOff& w, size_t& ro
     w.gpart_floats = fl;
     w.gtickets = take(kWsTickets * 4);
   }
-  w.lctrl = w.lssq = w.lerr = 0;
+  w.lctrl = w.lssq = 0;
   if (c->layers_ok) {
     w.lctrl = take(layers_ctrl_bytes());
     w.lssq = take((size_t)2 * kLayersMaxRows * (d / 16) * 4);
-    w.lerr = take(256);
   }
   w.ll = w.ctrl = w.head_all = w.tlog = 0;
   if (c->small_ok && !step_only) {
@@ -361,6 +360,10 @@ void forward_blocks(xsm_ctx* c, int n_seq, int R, int len_bound, hipStream_t s) 
   }
 }
 
+const uint32_t* layers_err(const xsm_ctx* c) {
+  return c->layers_ok ? (const uint32_t*)(c->d_w + c->layers_err_off) : nullptr;
+}
+
 // One pass of all layers as the persistent kernel; b names the rows (tokens or prefix embeddings).
 // kv_only: a prefill pass, whose result is the cache alone.
 void run_layers(xsm_ctx* c, LayersBegin b, bool kv_only, uint32_t* wflags, hipStream_t s) {
@@ -377,12 +380,15 @@ void run_layers(xsm_ctx* c, LayersBegin b, bool kv_only, uint32_t* wflags, hipSt
   a.gpart = (float*)(ws + c->ws.gpart); a.gtickets = (uint32_t*)(ws + c->ws.gtickets);
   a.x_out = (float*)(ws + c->ws.X);
   a.eff_len_w = (int32_t*)(ws + c->ws.eff_len); a.eff_len = a.eff_len_w; a.slot = (const int32_t*)(ws + c->ws.slot);
-  a.wflags = wflags; a.err = (uint32_t*)(ws + c->ws.lerr);
+  a.wflags = wflags; a.err = (uint32_t*)layers_err(c);
+  // (a step-only layout has no single-launch exchange)
+  a.err_small = c->small_ok && c->ws.ctrl ? (uint32_t*)(ws + c->ws.ctrl) + 1 : nullptr;
   a.rope = (const float2*)(c->d_w + c->rope_off); a.ctrl = (uint32_t*)(ws + c->ws.lctrl);
   a.eps = g.rms_eps; a.scale_log2 = 1.4426950408889634f / sqrtf((float)g.head_dim);
   a.cap = c->cap_self; a.cap_cross = c->cap_cross; a.n_cond = g.n_cond;
   b.gain = (const uint16_t*)layer_ptrs(c, 0).g1;
   b.eff_len = a.eff_len_w; b.slot_out = (int32_t*)(ws + c->ws.slot); b.wflags = wflags;
+  b.err = a.err;
   launch_layers(b, a, g.d_model, s);
 }
 
@@ -403,7 +409,7 @@ void run_tiled(xsm_ctx* c, LayersBegin b, bool kv_only, uint32_t* wflags, int le
   const int32_t* slot = (const int32_t*)(ws + c->ws.slot);
   b.gain = (const uint16_t*)layer_ptrs(c, 0).g1;
   b.eff_len = (int32_t*)(ws + c->ws.eff_len); b.slot_out = (int32_t*)(ws + c->ws.slot); b.wflags = wflags;
-  b.d = d; b.H = g.n_heads; b.x = x; b.planes = P; b.ssq = ssq;
+  b.err = layers_err(c); b.d = d; b.H = g.n_heads; b.x = x; b.planes = P; b.ssq = ssq;
   launch_layers_begin(b, s);
   TileGemm t0{};
   t0.M = M; t0.eps = g.rms_eps; t0.x = x; t0.P = P; t0.ssq_out = ssq;
@@ -564,7 +570,7 @@ int step_common(xsm_ctx* ctx, const xsm_batch* bt, const xsm_verify_params* vp, 
     run_tiled(ctx, b, false, wfl, bt->kv_len_bound, s);
   } else {
     launch_prepare(bt->kv_len, bt->slot, bt->block, n_seq, R, V, g.max_batch, g.max_ctx,
-                   bt->kv_len_bound, eff, slot, wfl, tick, s);
+                   bt->kv_len_bound, layers_err(ctx), eff, slot, wfl, tick, s);
     launch_embed(dt, wb + ctx->woff.E * e, bt->block, eff, X, n_seq, R, d, s);
     forward_blocks(ctx, n_seq, R, bt->kv_len_bound, s);
   }
@@ -732,6 +738,8 @@ int xsm_create(const xsm_config* cfg, xsm_ctx** out) {
   if (c->layers_ok) {
     c->layer_wts_off = c->weights_bytes;
     c->weights_bytes += align_up(sizeof(LayerWts) * g.n_layers);
+    c->layers_err_off = c->weights_bytes;
+    c->weights_bytes += align_up(4);
   }
   c->kv_self_elems = (size_t)g.n_layers * 2 * g.max_batch * g.n_heads * c->cap_self * g.head_dim;
   c->kv_cross_elems = (size_t)g.n_layers * 2 * g.max_batch * g.n_heads * c->cap_cross * g.head_dim;
@@ -830,7 +838,7 @@ int xsm_load_weights(xsm_ctx* ctx, const void* h_canonical, size_t n_elems, xsm_
       }
       XSM_HIP(hipMemcpyAsync(wb + ctx->layer_wts_off, ctx->layer_wts.data(), sizeof(LayerWts) * g.n_layers,
                              hipMemcpyHostToDevice, s));
-      launch_fill_i32((int32_t*)(ctx->d_ws + ctx->ws.lerr), 1, 0, s);
+      launch_fill_i32((int32_t*)(ctx->d_w + ctx->layers_err_off), 1, 0, s);
     }
     if (ctx->small_ok) {
       ctx->layer_tab.resize(g.n_layers);
@@ -1016,42 +1024,39 @@ int xsm_check_device(xsm_ctx* ctx) {
   if (!ctx) return XSM_EINVAL;
   XSM_HIP(hipDeviceSynchronize());
   if (!ctx->d_ws || !ctx->loaded) return XSM_OK;
-  if (ctx->layers_ok) {
-    uint32_t code = 0;
-    XSM_HIP(hipMemcpy(&code, ctx->d_ws + ctx->ws.lerr, 4, hipMemcpyDeviceToHost));
-    if (code != 0) {
-      // (attention's arrival counters may be half way: they start at zero again)
-      const uint32_t zero = 0;
-      XSM_HIP(hipMemcpy(ctx->d_ws + ctx->ws.lerr, &zero, 4, hipMemcpyHostToDevice));
-      clear_tickets(ctx, nullptr);
-      XSM_HIP(hipDeviceSynchronize());
-      ctx->layers_failed = true;
-      return fail(ctx, XSM_EDEVICE, "layers kernel: a wait for a stage timed out (code " + std::to_string(code) +
-                                        "); the sequences of that step carry n_accepted = 0 and XSM_FLAG_DEVICE_TIMEOUT, "
-                                        "later passes run on the per-stage kernels");
-    }
-  }
-  if (!ctx->small_ok) return XSM_OK;
-  uint32_t c[2] = {0, 0};
-  XSM_HIP(hipMemcpy(c, ctx->d_ws + ctx->ws.ctrl, 8, hipMemcpyDeviceToHost));
+  const uint32_t zero = 0;
+  uint32_t lcode = 0, c[2] = {0, 0};
+  if (ctx->layers_ok) XSM_HIP(hipMemcpy(&lcode, ctx->d_w + ctx->layers_err_off, 4, hipMemcpyDeviceToHost));
+  if (ctx->small_ok) XSM_HIP(hipMemcpy(c, ctx->d_ws + ctx->ws.ctrl, 8, hipMemcpyDeviceToHost));
+  // reported once: the error words are cleared and this context's later passes take the per-stage
+  // kernels (the exchange buffers may hold half a step; loading weights again resets them)
   if (c[1] != 0) {
-    // reported once: the error word is cleared and this context's later steps take the per-stage
-    // kernels (the exchange buffers may hold half a step; loading weights again resets them)
-    const uint32_t zero = 0;
     XSM_HIP(hipMemcpy(ctx->d_ws + ctx->ws.ctrl + 4, &zero, 4, hipMemcpyHostToDevice));
     ctx->small_failed = true;
+  }
+  if (lcode != 0) {
+    XSM_HIP(hipMemcpy(ctx->d_w + ctx->layers_err_off, &zero, 4, hipMemcpyHostToDevice));
+    clear_tickets(ctx, nullptr);     // (attention's arrival counters may be half way: they start at zero again)
+    XSM_HIP(hipDeviceSynchronize());
+    ctx->layers_failed = true;
+    return fail(ctx, XSM_EDEVICE, "layers kernel: a wait for a stage timed out (code " + std::to_string(lcode) +
+                                      "); the sequences of that pass and of later steps carry n_accepted = 0 and "
+                                      "XSM_FLAG_DEVICE_TIMEOUT, from here on passes run on the per-stage kernels");
+  }
+  if (c[1] != 0)
     return fail(ctx, XSM_EDEVICE, "single-launch step: a wait for stage inputs timed out (stage code " +
                                       std::to_string(c[1]) + "); the sequences of that step carry n_accepted = 0 and "
                                       "XSM_FLAG_DEVICE_TIMEOUT, later steps run on the per-stage kernels");
-  }
   return XSM_OK;
 }
 
 int xsm_debug_inject_device_error(xsm_ctx* ctx, uint32_t code) {
   if (!ctx) return XSM_EINVAL;
-  if (!ctx->small_ok || !ctx->d_ws || !ctx->loaded) return fail(ctx, XSM_ESTATE, "no single-launch step for this model");
+  if ((!ctx->small_ok && !ctx->layers_ok) || !ctx->d_ws || !ctx->loaded)
+    return fail(ctx, XSM_ESTATE, "no persistent kernel for this model");
   XSM_HIP(hipDeviceSynchronize());
-  XSM_HIP(hipMemcpy(ctx->d_ws + ctx->ws.ctrl + 4, &code, 4, hipMemcpyHostToDevice));
+  if (ctx->small_ok) XSM_HIP(hipMemcpy(ctx->d_ws + ctx->ws.ctrl + 4, &code, 4, hipMemcpyHostToDevice));
+  if (ctx->layers_ok) XSM_HIP(hipMemcpy(ctx->d_w + ctx->layers_err_off, &code, 4, hipMemcpyHostToDevice));
   return XSM_OK;
 }
 

@@ -34,7 +34,7 @@ struct WorkOff {
   size_t eff_len, slot, acc, y0, wflags, rowidx, arrived, eff2, slot2;   // int32 arrays
   size_t part, tickets, gpart, gtickets;                                  // split-key attention partials
   size_t ll, ctrl, head_all, tlog;                       // single-launch step: exchange buffers
-  size_t lctrl, lssq, lerr;                              // persistent layers kernel: queues and partition, square sums, error word
+  size_t lctrl, lssq;                                    // persistent layers kernel: queues and partition, square sums
   size_t gpart_floats;                                   // size of gpart
   size_t total;
 };
@@ -95,6 +95,7 @@ struct xsm_ctx {
   bool tile_ok = false;    // row- and column-blocked projections of large passes available for this model shape
   bool layers_ok = false;  // persistent layers kernel available for this model shape
   size_t layer_wts_off = 0;              // byte offset of the LayerWts array in the weights buffer
+  size_t layers_err_off = 0;             // and of the layers kernel's error word (it outlives the workspace's contents)
   std::vector<xsm::LayerWts> layer_wts;  // host copy (source of the upload)
   bool timeline = false;   // xsm_set_option(XSM_OPT_TIMELINE)
   int force_splits = 0;    // xsm_set_option(XSM_OPT_ATTN_SPLITS): key-range slices per (sequence, head), 0 = automatic
@@ -153,7 +154,7 @@ void launch_rope_table(float2* tab, int max_ctx, int head_dim, float theta, hipS
 // flag bits.
 void launch_prepare(const int32_t* kv_len, const int32_t* slot, const int32_t* block, int n_seq,
                     int R, int vocab, int max_batch, int max_ctx, int kv_len_bound,
-                    int32_t* eff_len, int32_t* slot_out, uint32_t* wflags, uint32_t* arrived, hipStream_t s);
+                    const uint32_t* err, int32_t* eff_len, int32_t* slot_out, uint32_t* wflags, uint32_t* arrived, hipStream_t s);
 void launch_fill_i32(int32_t* p, int n, int32_t v, hipStream_t s);
 
 void launch_embed(int dtype, const void* E, const int32_t* block, const int32_t* eff_len, float* X,
@@ -253,6 +254,7 @@ struct LayersBegin {
   const uint16_t* gain;                 // first norm
   int n_seq, R, d, H, vocab, max_batch, max_ctx, bound;
   int32_t* eff_len; int32_t* slot_out; uint32_t* wflags;
+  const uint32_t* err;                  // not 0: an earlier pass of the layers kernel gave up, every sequence is skipped (may be null)
   uint32_t* arrived;                    // decoding: counters of the step's tail, one per sequence, cleared
   int partition;                        // 1: also attention's shares and cleared queues (xsm_layers.hip)
   float* x; void* planes; float* ssq; uint32_t* ctrl; int32_t* unit_pre;                 // (set by launch_layers)
@@ -264,6 +266,7 @@ struct LayersArgs {
   float* q; void* AO; void* U; float* part; uint32_t* tickets; float* gpart; uint32_t* gtickets;
   float* x_out;                         // final residual rows [M][d]
   const int32_t* eff_len; int32_t* eff_len_w; const int32_t* slot; uint32_t* wflags; uint32_t* err;
+  uint32_t* err_small;                  // the single-launch step's error word (may be null)
   const float2* rope; uint32_t* ctrl; const int32_t* unit_pre;
   float eps, scale_log2;
   int cap, cap_cross, n_cond;

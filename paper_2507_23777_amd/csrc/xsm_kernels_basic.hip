@@ -30,10 +30,10 @@ void launch_rope_table(float2* tab, int max_ctx, int head_dim, float theta, hipS
 // ---------------------------------------------------------------------------
 __global__ void k_prepare(const int32_t* kv_len, const int32_t* slot, const int32_t* block,
                           int n_seq, int R, int vocab, int max_batch, int max_ctx, int bound,
-                          int32_t* eff_len, int32_t* slot_out, uint32_t* wflags, uint32_t* arrived) {
+                          const uint32_t* err, int32_t* eff_len, int32_t* slot_out, uint32_t* wflags, uint32_t* arrived) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= n_seq) return;
-  uint32_t f = 0;
+  uint32_t f = err && *err ? XSM_FLAG_DEVICE_TIMEOUT : 0;   // (a pass in front gave up: the cache may be half written)
   const int n = kv_len[b], sl = slot[b];
   if (n < 0 || n + R > max_ctx || n > bound) f |= XSM_FLAG_BAD_LEN;
   if (sl < 0 || sl >= max_batch) f |= XSM_FLAG_BAD_SLOT;
@@ -48,10 +48,10 @@ __global__ void k_prepare(const int32_t* kv_len, const int32_t* slot, const int3
 }
 void launch_prepare(const int32_t* kv_len, const int32_t* slot, const int32_t* block, int n_seq,
                     int R, int vocab, int max_batch, int max_ctx, int kv_len_bound,
-                    int32_t* eff_len, int32_t* slot_out, uint32_t* wflags, uint32_t* arrived, hipStream_t s) {
+                    const uint32_t* err, int32_t* eff_len, int32_t* slot_out, uint32_t* wflags, uint32_t* arrived, hipStream_t s) {
   TraceScope trace_("prepare", s);
   hipLaunchKernelGGL(k_prepare, dim3((n_seq + 63) / 64), dim3(64), 0, s, kv_len, slot, block, n_seq,
-                     R, vocab, max_batch, max_ctx, kv_len_bound, eff_len, slot_out, wflags, arrived);
+                     R, vocab, max_batch, max_ctx, kv_len_bound, err, eff_len, slot_out, wflags, arrived);
 }
 
 __global__ void k_fill_i32(int32_t* p, int n, int32_t v) {

@@ -38,7 +38,8 @@
 // always belongs to a running workgroup that waits for nothing, however few workgroups are resident
 // (another stream's kernel may hold compute units), so the grid drains without needing to be
 // co-resident.  Waits are bounded all the same: a workgroup that gives up marks every sequence
-// as skipped (XSM_FLAG_DEVICE_TIMEOUT) and raises the error word of xsm_check_device.
+// as skipped (XSM_FLAG_DEVICE_TIMEOUT) and raises the error word of xsm_check_device; until that has
+// reported it, every pass that starts finds the word and skips all of its sequences.
 #include <type_traits>
 #include "xsm_attn_device.h"
 #include "xsm_internal.h"
@@ -120,7 +121,7 @@ __device__ __forceinline__ float gelu_erf_f(float x) { return 0.5f * x * (1.0f +
 // One workgroup per row, one more for the rest.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t seq_flags(const LayersBegin& a, int b, int* len, int* slot) {
-  uint32_t f = 0;
+  uint32_t f = a.err && *a.err ? XSM_FLAG_DEVICE_TIMEOUT : 0;
   const int n = a.kv_len[b], sl = a.slot[b];
   if (n < 0 || n + a.R > a.max_ctx || n > a.bound) f |= XSM_FLAG_BAD_LEN;
   if (sl < 0 || sl >= a.max_batch) f |= XSM_FLAG_BAD_SLOT;
@@ -169,7 +170,7 @@ __global__ __launch_bounds__(256) void k_layers_begin(const LayersBegin a) {
   if (a.partition)
     for (int i = tid; i < 2 * kQueues * kQueueStride; i += 256) a.ctrl[i] = 0;
   for (int b = tid; b < a.n_seq; b += 256) {
-    int len = a.row0, sl = 0;
+    int len = a.err && *a.err ? -1 : a.row0, sl = 0;
     if (!a.rows) {
       const uint32_t f = seq_flags(a, b, &len, &sl);
       if (f) len = -1;
@@ -929,7 +930,10 @@ __global__ __launch_bounds__(kThreads) void k_layers(const LayersArgs a) {
       st_coh(a.eff_len_w + b, -1);
       if (a.wflags) st_coh(a.wflags + b, (uint32_t)XSM_FLAG_DEVICE_TIMEOUT);
     }
-    if (lane == 0 && a.err) st_coh(a.err, 0x4C000000u | (uint32_t)task);
+    if (lane == 0) {
+      st_coh(a.err, 0x4C000000u | (uint32_t)task);
+      if (a.err_small) st_coh(a.err_small, 0x4C000000u | (uint32_t)task);
+    }
   }
 }
 

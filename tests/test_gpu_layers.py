@@ -67,3 +67,34 @@ def test_cross_attention(X, n_seq, n_cond):
     tal = X.H.lockstep(cfg, orc, states, eng, X.xsm, vp, 2, si.first_block(cfg, n_seq))
     _report(tal, f"layers kernel cross-attention B{n_seq} n_cond {n_cond}")
     eng.xsm_check_device()
+
+
+def test_timeout_is_reported_in_band_and_falls_back(X):
+    """The failure path, forced from the host (the error word is set as a timed-out wait would set it; no
+    wait is made to spin and every kernel exits normally): steps and prefills enqueued before the report
+    change nothing and say so, and the passes after it run on the per-stage kernels and match the oracle."""
+    cfg = _c1_small(n_layers=2, n_draft=2, vocab=1024)
+    torch, lens = X.torch, [40, 3, 64, 61, 128, 17]
+    w, orc, states, eng = X.H.setup_pair(cfg, X.pkg.Engine, 6, prefix_lens=lens)
+    first = si.first_block(cfg, 6)
+    buf = eng.buffers(6, spec=True)
+    buf.kv_len.copy_(torch.tensor(lens)); buf.block.copy_(torch.tensor(first))
+    buf.out_tokens.fill_(-7)
+    eng.xsm_debug_inject_device_error(77)
+    for _ in range(2):
+        eng.xsm_spec_step(buf, X.H.to_vp_gpu(X.xsm, GREEDY), max(lens))
+    eng.xsm_prefill([0, 2], torch.ones(2, 20, cfg["d_model"], dtype=torch.bfloat16, device="cuda:0"))
+    eng.xsm_prefill([4], torch.ones(1, 19, cfg["d_model"], dtype=torch.bfloat16, device="cuda:0"))
+    torch.cuda.synchronize()
+    assert buf.n_accepted.tolist() == [0] * 6
+    assert all(int(f) & X.xsm.XSM_FLAG_DEVICE_TIMEOUT for f in buf.flags.tolist())
+    assert buf.kv_len.tolist() == lens and buf.block.tolist() == first.tolist()
+    assert (buf.out_tokens == -7).all()
+    with pytest.raises(X.xsm.XsmError, match="timed out"):
+        eng.xsm_check_device()
+    eng.xsm_check_device()                               # reported once
+    X.xsm.xsm_debug_trace_enable(True); X.xsm.xsm_debug_trace_report()
+    tal = X.H.lockstep(cfg, orc, states, eng, X.xsm, GREEDY, 2, first)
+    ran = X.xsm.xsm_debug_trace_report(); X.xsm.xsm_debug_trace_enable(False)
+    _report(tal, "after the layers kernel's injected timeout: per-stage kernels")
+    assert "gemm_ws" in ran, sorted(ran)
